@@ -191,6 +191,45 @@ def run(state):
     return bcq.bcq_gemm_mixed(state["planes"], state["scales"], state["p_req"], state["x"], group=case["group"], offsets_by_p=state["offsets"])
 
 
+def _weights64(planes, scales, offsets, group):
+    """W_p in 64 bits from the storage format: bit j of word k is column 32 k + j, set for +1."""
+    p, m, ngroups = scales.shape
+    w = torch.zeros((m, ngroups * group), dtype=torch.float64, device=planes.device)
+    shifts = torch.arange(32, dtype=torch.int32, device=planes.device)
+    for i in range(p):
+        bits = ((planes[i].unsqueeze(-1) >> shifts) & 1).reshape(m, ngroups, group)
+        w += ((2 * bits - 1) * scales[i].double().unsqueeze(-1)).reshape(m, -1)
+    if offsets is not None:
+        w += offsets.double().repeat_interleave(group, dim=1)
+    return w
+
+
+def _product64(planes, scales, offsets, group, x):
+    y = torch.empty((x.shape[0], planes.shape[1]), dtype=torch.float64, device=x.device)
+    for r in range(0, planes.shape[1], 4096):
+        rows = slice(r, r + 4096)
+        y[:, rows] = x.double() @ _weights64(planes[:, rows], scales[:, rows], None if offsets is None else offsets[rows], group).t()
+    return y
+
+
+def exact(case, seed):
+    """The results in 64 bits, without the library.  The quantiser has no such value: its scales are what its codes make them, and
+    both are compared bit for bit."""
+    if case["kind"] == "quantize":
+        return None
+    s = prepare(dict(case, graph=False), seed)
+    if case["kind"] == "blocks":
+        return [_product64(w, a, z, 128, t["x"]) for t in s["stages"]
+                for w, a, z in zip(t["planes"], t["scales"], t["offsets"] or [None] * len(t["planes"]))]
+    if case["p"]:
+        return _product64(s["planes"], s["scales"][case["p"]], s["offsets"][case["p"]] if s["offsets"] else None, case["group"], s["x"])
+    y = torch.empty((case["batch"], case["m"]), dtype=torch.float64, device="cuda")
+    for p, scales in s["scales"].items():
+        picked = (s["p_req"] == p).nonzero().flatten()
+        y[picked] = _product64(s["planes"], scales, s["offsets"][p] if s["offsets"] else None, case["group"], s["x"][picked])
+    return y
+
+
 def _product_bytes(m, n, p, scale_rows, group, offset_rows):
     return m * n // 8 * p + m * (n // group) * 2 * (scale_rows + offset_rows)
 
