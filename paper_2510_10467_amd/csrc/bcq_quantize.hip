@@ -188,6 +188,19 @@ __device__ __forceinline__ void greedy_plane(Lane &s)
     s.alpha[I] = group_sum<LANES>(acc) / (32.0 * LANES);
 }
 
+// The alternation stops early at a fixed point: a cycle is a function of the codes alone, so codes that come
+// out as they went in give the same scales and the same codes in every cycle that is left.  The lanes of a wave go on
+// together until none of their groups has changed a code (groups that have settled repeat themselves).  Normal weights
+// with a few outliers settle in a fraction of 20 cycles (4096 x 4096, p = 2 .. 4, T = 20: 446.5 -> 294.4 us).
+template <int P>
+__device__ __forceinline__ bool any_changed(const Lane &s, const uint32_t (&word)[P])
+{
+    uint32_t differ = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) differ |= word[i] ^ s.word[i];
+    return __ballot(differ != 0) != 0;
+}
+
 // T cycles at the base precision P: LS, then every weight takes the codes of its nearest level.
 template <int P, int LANES, bool OFFSET>
 __device__ __forceinline__ void base_stage(Lane &s, int cycles, double sum_w)
@@ -222,6 +235,7 @@ __device__ __forceinline__ void base_stage(Lane &s, int cycles, double sum_w)
 #pragma unroll
             for (int i = 0; i < P; ++i) word[i] |= (uint32_t)((best >> (P - 1 - i)) & 1) << j;
         }
+        if (!any_changed<P>(s, word)) break;
 #pragma unroll
         for (int i = 0; i < P; ++i) s.word[i] = word[i];
     }
@@ -245,7 +259,7 @@ __device__ __forceinline__ void base_stage_two(Lane &s, int cycles, double sum_w
             const double v = ((c & 2) ? s.alpha[0] : -s.alpha[0]) + ((c & 1) ? s.alpha[1] : -s.alpha[1]);
             lev[c] = OFFSET ? v + s.z : v;
         }
-        uint32_t word0 = 0, word1 = 0;
+        uint32_t word[2] = {0, 0};
         double acc0[2] = {0.0, 0.0}, acc1[2] = {0.0, 0.0};
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
@@ -256,13 +270,14 @@ __device__ __forceinline__ void base_stage_two(Lane &s, int cycles, double sum_w
             const double m01 = __builtin_fmin(d0, d1), m23 = __builtin_fmin(d2, d3);
             const bool top = m23 < m01;                 // plane 0: +1 for levels 2, 3
             const bool low = top ? c23 : c01;           // plane 1
-            word0 |= top ? (1u << j) : 0u;
-            word1 |= low ? (1u << j) : 0u;
+            word[0] |= top ? (1u << j) : 0u;
+            word[1] |= low ? (1u << j) : 0u;
             acc0[j & 1] += top ? wj : -wj;
             acc1[j & 1] += low ? wj : -wj;
         }
-        s.word[0] = word0;
-        s.word[1] = word1;
+        if (!any_changed<2>(s, word)) break;
+        s.word[0] = word[0];
+        s.word[1] = word[1];
         rhs_w[0] = group_sum<LANES>(acc0[0] + acc0[1]);
         rhs_w[1] = group_sum<LANES>(acc1[0] + acc1[1]);
     }
@@ -324,6 +339,8 @@ __device__ __forceinline__ void expand_stage(Lane &s, int cycles, double sum_w, 
             acc[j & 1] += flip(s.w[j], rhi & 0x80000000u);
         }
         __builtin_amdgcn_wave_barrier();
+        // (the first cycle starts from codes that were never chosen: nothing to compare with)
+        if (t > 0 && __ballot(~minus != own) == 0) break;
         s.word[P - 1] = ~minus;
         rhs_w[P - 1] = group_sum<LANES>(acc[0] + acc[1]);
         least_squares<P, LANES, OFFSET>(s, rhs_w, sum_w);
