@@ -1299,9 +1299,9 @@ constexpr WgShape kShapes[] = {{1, 4, 0.51f, 0.32f, 0.78f, 0.39f}, {1, 2, 0.36f,
                                // (128 requests and 128 rows the same way: 28672x8192 at 128 requests 139 -> 129 us)
                                {8, 8, 2.01f, 1.48f, 0.f, 0.f}};
 
-// the cheapest shape for `batch` requests at precision p, among the shapes of at least min_nt tiles; `times`: that
-// many such problems in one launch
-void cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, int times = 1)
+// the cheapest shape for `batch` requests at precision p and its cost, among the shapes of at least min_nt tiles; `times`:
+// that many such problems in one launch
+float cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, int times = 1)
 {
     nt = rw = 4;
     float best = 0.f;
@@ -1319,6 +1319,7 @@ void cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, i
             rw = c.rw;
         }
     }
+    return best;
 }
 
 // A batch with per-request precision beyond 64 requests: the uniform kernel's body on the requests of each
@@ -1384,6 +1385,8 @@ hipError_t launch_p(const DequantParams &pr, const GemmArgs &a, hipStream_t stre
 // request_tiles: 1, 2 or 4 tiles of 64 requests, or 0 (with row_blocks != 0) for a single tile of 16 requests
 bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
 {
+    if (request_tiles == 1 && row_blocks >= 100) return level_mfma_force_shape(row_blocks - 100);
+    level_mfma_force_shape(-1);
     if (request_tiles == 0 && row_blocks == 0) {
         g_forced_nt = g_forced_rw = 0;
         return true;
@@ -1434,6 +1437,19 @@ hipError_t dequant_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_
 
 hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool planewise, const GemmArgs *mats, int count)
 {
+    if (!planewise && a.uniform_p > 0) {
+        // More than 32 requests: the level form wherever its cheapest shape costs less than this one's (28672 x 8192 at 2048
+        // requests and p = 3: 1271 -> 963 us; 8192 x 8192 at 96 and p = 4: 51 -> 40); up to 32 its tiles stand partly empty.
+        const int forced = level_mfma_forced_shape();
+        if (forced >= 0) return level_mfma_supports(a) ? level_mfma_launch(a, forced, stream, mats, count) : hipErrorInvalidValue;
+        if (g_forced_nt == 0 && a.batch > 32 && level_mfma_supports(a)) {
+            int nt, rw;
+            float level_cost;
+            const float cost = cheapest_shape(a.uniform_p, a.m, a.batch, 1, nt, rw);
+            const int shape = level_mfma_cheapest(a.uniform_p, a.m, a.batch, 1, level_cost);
+            if (level_cost < cost) return level_mfma_launch(a, shape, stream, mats, count);
+        }
+    }
     DequantParams pr{};
     pr.planes = reinterpret_cast<const unsigned char *>(a.planes);
     pr.x = reinterpret_cast<const unsigned char *>(a.x);

@@ -67,6 +67,14 @@ hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool plane
 bool dequant_mfma_supports_multi(const GemmArgs *mats, int count);
 hipError_t dequant_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t stream, bool planewise);
 
+// The level form of the large-batch kernels: weights rebuilt by look-ups, tiles of 32 x 32 (dequant_mfma_launch picks it).
+bool level_mfma_supports(const GemmArgs &a);
+// its cheapest shape for `times` problems of m rows and `batch` requests in one launch, and the cost per 128 columns
+int level_mfma_cheapest(int p, int64_t m, int batch, int times, float &cost);
+bool level_mfma_force_shape(int shape);         // benchmarks and tests; -1: automatic
+int level_mfma_forced_shape();
+hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count);
+
 // Offline quantiser (Algorithm 1): group must be 32, 64, 128 or 256; 1 <= p_low <= p_high <= 4.
 bool quantize_supports(int64_t m, int64_t n, int group);
 hipError_t quantize_launch(const _Float16 *w, int p_low, int p_high, int cycles, uint32_t *planes, _Float16 *const *scales_by_p,

@@ -1,0 +1,550 @@
+// Large batches, the level form of the dequantising kernel: W_p is rebuilt by LOOKING UP its values instead of summing
+// them.  Inside a scale group a row has only 2^p different weights, the levels z + sum_i (+-alpha_i); a lane forms those of
+// its row once per group (the same fp32 sums in the same order, rounded once to binary16, that the other form makes for
+// every weight) and keeps them in four registers, the low bytes and the high bytes of eight levels.  The p plane
+// words of 32 columns become 32 codes of p bits in two byte transposes, and a V_PERM_B32 with four codes as its selector
+// delivers one byte of four weights.  That is about 2.5 vector instructions per weight (p = 3: bit transpose 13, byte
+// transpose 8, selectors 12 and look-ups 32 per 32 columns) where the sums take about six and two LDS reads per plane.
+//   p <= 3            2^p <= 8 levels, one pair of registers per byte
+//   p = 4             the levels come in pairs +-l: eight of them are kept, the codes of planes 0..2 are complemented where
+//                     plane 3 is -1 and the sign goes onto the high byte
+//   p = 4, offsets    sixteen levels, two look-ups per byte and a select
+//
+// The product runs on v_mfma_f32_32x32x16_f16: a wave owns RT tiles of 32 rows and QT tiles of 32 requests.  Against 16 x 16
+// tiles an instruction needs half as many operand reads from LDS per operation, and it leaves the SIMD's issue slots free for
+// half of its 32 cycles, which is where the look-ups go.  The two lane halves hold the two 128-column groups of a pair
+// of groups (a permutation of K which the activations follow), so that a lane sees one group and one set of levels:
+//   step of 16 columns = columns c .. c+7 of group 2G (lanes 0-31) and of group 2G+1 (lanes 32-63).
+// A stage is 64 columns (word w of both groups).  Its activations are staged in LDS, by loads that write LDS directly, three
+// stages ahead in a ring of four tiles; at the barrier that ends a stage the tile AFTER the next one has landed (what this
+// stage asked for stays under way: the wait is for all but the last XU loads), so the operands of the next stage's first
+// step are read before the barrier and nothing waits behind it.  The eight 16-byte parts of a request sit XOR-permuted by the
+// request number, so that the operand reads of sixteen requests use all banks.  The weights of a step are made during
+// the step before it, a few look-ups after each matrix instruction (left to itself the compiler reads two operands, waits
+// for them and issues two matrix instructions).
+//
+// A workgroup is TEAMS teams of WR x WQ waves; the teams take alternate pairs of groups with tiles of their own and meet at
+// the end (short matrices: rows alone do not fill the chip).
+//
+// What bounds it: matrix instructions and, with the chip full and random data, power: 28672 x 8192 with 2048 requests at p = 3
+// 1203 -> 923 us = 1042 TFLOP/s, where the library's plain fp16 product of 8192^3 reaches 1211 (1751 with zeros).  Smaller
+// tiles are bound by the look-ups (four matrix instructions of 32 cycles and about 30 vector instructions of 4 per step of
+// 32 rows x 128 requests).  8192 x 8192 in groups of 64 with 96 requests 47.8 -> 38.1 us; the linear layers of a Llama-3-8B
+// block with 500 requests at p = 4 422 -> 332 us.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "bcq_internal.hpp"
+
+namespace bcq {
+namespace {
+
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMaxP = 4;
+constexpr int kRowBytes = 128;              // LDS row of one request: the 64 columns of a stage
+constexpr int kRing = 4;                    // stages in LDS
+// vector instructions placed between two matrix instructions
+template <int QT> constexpr int kBetween = QT >= 8 ? 4 : QT >= 4 ? 6 : 12;
+
+struct LevelParams {
+    const unsigned char *planes, *scales, *offsets, *x;
+    _Float16 *y;
+    uint32_t plane_stride, row_stride;      // bytes between planes (m n / 8) and plane rows (n / 8)
+    uint32_t scale_plane_stride, scale_row_stride;      // bytes between scale planes (m n / group * 2) and rows
+    uint32_t x_stride;                      // bytes between requests: n * 2
+    uint32_t m;
+    int batch, npairs;                      // npairs: pairs of 128-column groups
+    int gshift;                             // scale groups of 64 (-1), 128 (0) or 256 (+1) columns
+    // per-request precision: a scale / offset set per precision, nullptr where there is none
+    const unsigned char *scale_sets[kMaxP + 1];
+    const unsigned char *offset_sets[kMaxP + 1];
+    const int32_t *p_req;
+    int p_max;
+    uint32_t class_order;                   // byte y = the precision served by the workgroups with blockIdx.y = y
+    // several matrices in one launch (nmat > 1): matrix k owns the workgroup rows mat_blk0[k] .. mat_blk0[k+1]-1
+    int nmat;
+    const unsigned char *mat_planes[BCQ_MAX_MULTI];
+    const unsigned char *mat_scales[BCQ_MAX_MULTI];
+    _Float16 *mat_y[BCQ_MAX_MULTI];
+    uint32_t mat_m[BCQ_MAX_MULTI];
+    uint32_t mat_blk0[BCQ_MAX_MULTI];
+};
+
+// a where the mask bit is set, b elsewhere
+__device__ __forceinline__ uint32_t pick_bits(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
+
+// The levels of one row and group, low and high bytes apart: byte c of lo[0] is the low byte of level c, of lo[1] of level 4 + c.
+template <int P, bool OFFSET>
+struct Levels {
+    static constexpr bool kSigned = P == 4 && !OFFSET;      // eight of the sixteen, those with plane 3 at +1
+    static constexpr int NQ = P <= 2 ? 1 : P == 3 || kSigned ? 2 : 4;       // quadruples of levels
+    uint32_t lo[NQ], hi[NQ];
+
+    // alpha[i], z: binary16 bits
+    __device__ __forceinline__ void form(const uint32_t (&alpha)[P], uint32_t z)
+    {
+        constexpr int NL = 4 * NQ;
+        float a[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) a[i] = (float)__builtin_bit_cast(_Float16, (unsigned short)alpha[i]);
+        float v[NL];
+        v[0] = OFFSET ? (float)__builtin_bit_cast(_Float16, (unsigned short)z) : 0.f;
+        // level of code c: bit i set means +alpha_i; plane 0 first, as the planes are summed
+        int have = 1;
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            if (kSigned && i == 3) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c) v[c] = v[c] + a[3];
+            } else {
+#pragma unroll
+                for (int c = 0; c < NL / 2; ++c)
+                    if (c < have) {
+                        v[(have + c) % NL] = v[c] + a[i];
+                        v[c] = v[c] - a[i];
+                    }
+                have *= 2;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < NQ; ++k) {
+            uint32_t h[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float f = 4 * k + c < (kSigned ? 8 : 1 << P) ? v[4 * k + c] : 0.f;
+                h[c] = __builtin_bit_cast(unsigned short, (_Float16)f);      // the single rounding of W_p to binary16
+            }
+            const uint32_t h01 = h[0] | (h[1] << 16), h23 = h[2] | (h[3] << 16);
+            lo[k] = __builtin_amdgcn_perm(h23, h01, 0x06040200u);
+            hi[k] = __builtin_amdgcn_perm(h23, h01, 0x07050301u);
+        }
+    }
+
+    // bytes of the codes of four columns (one code per byte; bits above the code are garbage) -> two dwords of two weights
+    __device__ __forceinline__ void weights(uint32_t codes, uint32_t sign, uint32_t &d0, uint32_t &d1) const
+    {
+        constexpr uint32_t mask = P == 1 ? 0x01010101u : P == 2 ? 0x03030303u : 0x07070707u;
+        const uint32_t sel = codes & mask;
+        uint32_t l, h;
+        if constexpr (NQ == 1) {
+            l = __builtin_amdgcn_perm(0u, lo[0], sel);
+            h = __builtin_amdgcn_perm(0u, hi[0], sel);
+        } else {
+            l = __builtin_amdgcn_perm(lo[1], lo[0], sel);
+            h = __builtin_amdgcn_perm(hi[1], hi[0], sel);
+        }
+        if constexpr (NQ == 4) {
+            const uint32_t one = (codes >> 3) & 0x01010101u, upper = (one << 8) - one;        // 0xff in the bytes of codes 8..15
+            l = pick_bits(upper, __builtin_amdgcn_perm(lo[3], lo[2], sel), l);
+            h = pick_bits(upper, __builtin_amdgcn_perm(hi[3], hi[2], sel), h);
+        }
+        if constexpr (kSigned) h ^= sign & 0x80808080u;
+        d0 = __builtin_amdgcn_perm(h, l, 0x05010400u);
+        d1 = __builtin_amdgcn_perm(h, l, 0x07030602u);
+    }
+};
+
+// 32 columns of P planes -> codes: byte c of out[t] holds the code of column 8t + c in its low nibble and that of column
+// 8t + 4 + c in its high nibble (bit i: plane i; bits of planes that are not there are garbage)
+template <int P, bool SIGNED>
+__device__ __forceinline__ void transpose_codes(const uint32_t (&w)[P], uint32_t (&out)[4])
+{
+    uint32_t t[4];
+    if constexpr (P == 1) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) t[c] = w[0] >> c;
+    } else {
+        uint32_t w0 = w[0], w1 = w[1];
+        if constexpr (SIGNED) {
+            w0 = ~(w0 ^ w[3]);
+            w1 = ~(w1 ^ w[3]);
+        }
+        const uint32_t a01 = pick_bits(0x55555555u, w0, w1 << 1), b01 = pick_bits(0x55555555u, w0 >> 1, w1);
+        if constexpr (P == 2) {
+            t[0] = a01;
+            t[1] = b01;
+            t[2] = a01 >> 2;
+            t[3] = b01 >> 2;
+        } else {
+            uint32_t a23, b23;
+            if constexpr (P == 3) {
+                a23 = w[2];
+                b23 = w[2] >> 1;
+            } else {
+                const uint32_t w2 = SIGNED ? ~(w[2] ^ w[3]) : w[2], w3 = SIGNED ? ~w[3] : w[3];
+                a23 = pick_bits(0x55555555u, w2, w3 << 1);
+                b23 = pick_bits(0x55555555u, w2 >> 1, w3);
+            }
+            t[0] = pick_bits(0x33333333u, a01, a23 << 2);
+            t[2] = pick_bits(0x33333333u, a01 >> 2, a23);
+            t[1] = pick_bits(0x33333333u, b01, b23 << 2);
+            t[3] = pick_bits(0x33333333u, b01 >> 2, b23);
+        }
+    }
+    const uint32_t p01 = __builtin_amdgcn_perm(t[1], t[0], 0x05010400u), q01 = __builtin_amdgcn_perm(t[1], t[0], 0x07030602u);
+    const uint32_t p23 = __builtin_amdgcn_perm(t[3], t[2], 0x05010400u), q23 = __builtin_amdgcn_perm(t[3], t[2], 0x07030602u);
+    out[0] = __builtin_amdgcn_perm(p23, p01, 0x05040100u);
+    out[1] = __builtin_amdgcn_perm(p23, p01, 0x07060302u);
+    out[2] = __builtin_amdgcn_perm(q23, q01, 0x05040100u);
+    out[3] = __builtin_amdgcn_perm(q23, q01, 0x07060302u);
+}
+
+// QT tiles of 32 requests per wave (and one of 32 rows), WR x WQ waves per team
+template <int QT_, int WR_, int WQ_, int TEAMS_>
+struct Shape {
+    static constexpr int QT = QT_, WR = WR_, WQ = WQ_, TEAMS = TEAMS_;
+    static constexpr int ROWS = 32 * WR, REQS = 32 * QT * WQ;
+    static constexpr int SW = WR * WQ;                              // waves of a team
+    static constexpr int THREADS = 64 * SW * TEAMS;
+    static constexpr int TILE = REQS * kRowBytes;                   // one stage's activations
+    static constexpr int XU = TILE / 1024 / SW;                     // loads of 1 KiB per wave and stage
+    static constexpr int LDS = TEAMS * kRing * TILE;
+    static_assert(XU * 1024 * SW == TILE && XU >= 1, "tile does not split over the team");
+    static_assert((TEAMS - 1) * SW * QT * 4096 <= LDS, "accumulator exchange must fit in the tiles");
+    static_assert(LDS + REQS * 4 <= 160 * 1024, "tiles and request numbers must fit in LDS");
+};
+
+// BYCLASS: the workgroup serves `nreq` requests whose numbers are in req_of (LDS); otherwise requests b0 .. of the batch.
+template <int P, typename S, bool OFFSET, bool BYCLASS>
+__device__ __forceinline__ void level_body(const LevelParams &a, const int b0, const int nreq, const uint32_t *req_of, const uint32_t rowblk)
+{
+    constexpr int QT = S::QT, TEAMS = S::TEAMS, XU = S::XU, SW = S::SW;
+    constexpr int UT = QT < 4 ? QT : 4;       // request tiles whose operands are held at a time
+    constexpr int NC = QT / UT;
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    using L = Levels<P, OFFSET>;
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int team = wave / SW, tw = wave % SW, wr = tw % S::WR, wq = tw / S::WR;
+    const int r32 = lane & 31, half = lane >> 5;
+    unsigned char *xt = lds + team * kRing * S::TILE;
+    const uint32_t row0 = rowblk * S::ROWS + wr * 32;
+
+    // rows and requests past the end repeat the last one (their results are not stored)
+    const uint32_t my_row = min(row0 + r32, a.m - 1);
+    uint32_t w_off = my_row * a.row_stride + half * 16;
+    uint32_t s_off = my_row * a.scale_row_stride + (a.gshift > 0 ? 0u : a.gshift < 0 ? half * 4u : half * 2u);
+    const uint32_t s_pair = a.gshift > 0 ? 2u : a.gshift < 0 ? 8u : 4u;      // bytes of a row's scales per pair of groups
+    // Load i of a stage brings the 1 KiB of requests 8i .. 8i+7; lane l delivers part (l & 7) ^ (request / 2 & 7) of request
+    // 8i + (l >> 3).  Parts 0-3 are columns 32w .. of the pair's first group, 4-7 of its second.
+    uint32_t xs_src[XU];
+#pragma unroll
+    for (int k = 0; k < XU; ++k) {
+        const int req = 8 * (k * SW + tw) + (lane >> 3);
+        const int part = (lane & 7) ^ ((req >> 1) & 7);
+        const uint32_t source = BYCLASS ? req_of[min(req, nreq - 1)] : (uint32_t)(b0 + min(req, nreq - 1));
+        xs_src[k] = source * a.x_stride + (part >> 2) * 256 + (part & 3) * 16;
+    }
+    // (buffer loads: the compiler counts loads of the global kind that write LDS among the LDS reads under way as well, and
+    // then waits for all of those reads wherever it needs one)
+    const auto x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.x), 0, (int)((uint32_t)a.batch * a.x_stride), 0x00020000);
+    auto stage_unit = [&](int pair, int w, int k) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (__attribute__((address_space(3))) void *)(xt + w * S::TILE + (k * SW + tw) * 1024), 16,
+                                                 (int)xs_src[k], pair * 512 + w * 64, 0, 0);
+    };
+    u32x4 word[P], word_n[P];
+    uint32_t sc[P], later[P], zc = 0, later_z = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i) sc[i] = 0;
+    auto fetch = [&](int pair) {
+        asm volatile("" : "+v"(w_off), "+v"(s_off));    // lane offsets stay 32 bits wide, in the load's own addressing mode
+#pragma unroll
+        for (int i = 0; i < P; ++i)
+            word_n[i] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + (uint32_t)pair * 32 + w_off);
+        const uint32_t col = (uint32_t)pair * s_pair;
+        if (a.gshift < 0) {
+#pragma unroll
+            for (int i = 0; i < P; ++i) sc[i] = *reinterpret_cast<const uint32_t *>(a.scales + (size_t)i * a.scale_plane_stride + col + s_off);
+            if (OFFSET) zc = *reinterpret_cast<const uint32_t *>(a.offsets + col + s_off);
+        } else {
+#pragma unroll
+            for (int i = 0; i < P; ++i) sc[i] = *reinterpret_cast<const unsigned short *>(a.scales + (size_t)i * a.scale_plane_stride + col + s_off);
+            if (OFFSET) zc = *reinterpret_cast<const unsigned short *>(a.offsets + col + s_off);
+        }
+    };
+
+    // operand reads: request 32 (wq QT + q) + r32, part 4 half + s
+    const unsigned char *xa_lane = xt + (wq * QT * 32 + r32) * kRowBytes;
+    const uint32_t xa_off = (uint32_t)(((4 * half) ^ ((r32 >> 1) & 7)) * 16);
+    auto operand = [&](int t, int u) {          // step t of a pair
+        return *reinterpret_cast<const v8h *>(xa_lane + (t >> 2) * S::TILE + u * (32 * kRowBytes) + (xa_off ^ (uint32_t)(16 * (t & 3))));
+    };
+
+    v16f acc[QT];
+#pragma unroll
+    for (int q = 0; q < QT; ++q)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
+
+    L lev;
+    uint32_t codes[4];
+    auto begin_pair = [&]() {                   // the words and scales that fetch() brought become the current ones
+        uint32_t first[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            word[i] = word_n[i];
+            first[i] = sc[i] & 0xffffu;
+            later[i] = sc[i] >> 16;
+        }
+        later_z = zc >> 16;
+        lev.form(first, zc & 0xffffu);
+    };
+    auto make = [&](int t) {                    // weights of step t of a pair
+        if (t == 8 && a.gshift < 0) lev.form(later, later_z);       // groups of 64: columns 64 .. of both groups
+        if ((t & 3) == 0) {
+            uint32_t w[P];
+#pragma unroll
+            for (int i = 0; i < P; ++i) w[i] = word[i][t >> 2];
+            transpose_codes<P, L::kSigned>(w, codes);
+        }
+        const uint32_t c = codes[t & 3];
+        uint32_t d0, d1, d2, d3;
+        lev.weights(c, c << 4, d0, d1);
+        lev.weights(c >> 4, c, d2, d3);
+        return __builtin_bit_cast(v8h, u32x4{d0, d1, d2, d3});
+    };
+
+    const int last = a.npairs - 1;
+    if (team <= last) {
+        fetch(team);
+#pragma unroll
+        for (int w = 0; w < kRing - 1; ++w)
+#pragma unroll
+            for (int k = 0; k < XU; ++k) stage_unit(team, w, k);
+    }
+    asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+    v8h wb, xa[UT];
+    if (team <= last) {
+        begin_pair();
+        wb = make(0);
+#pragma unroll
+        for (int u = 0; u < UT; ++u) xa[u] = operand(0, u);
+    }
+    const int rounds = (a.npairs + TEAMS - 1) / TEAMS;
+    for (int it = 0; it < rounds; ++it) {
+        const int pair = it * TEAMS + team;
+        if (pair > last) {                      // a team without a pair of its own in the last round meets the barriers
+            asm volatile("s_barrier\n\ts_barrier\n\ts_barrier\n\ts_barrier" ::: "memory");
+            continue;
+        }
+        const int npair = min(pair + TEAMS, last);                  // (past the end: something that is there, for nothing)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            v8h wn, xn[UT];
+            if (t == 4) fetch(npair);
+#pragma unroll
+            for (int k = 0; k < XU; ++k)
+                if (k * 4 / XU == (t & 3)) stage_unit(t < 4 ? pair : npair, ((t >> 2) + kRing - 1) & (kRing - 1), k);
+            if (t == 15) begin_pair();
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                const int tn = c + 1 < NC ? t : (t + 1) & 15, cn = c + 1 < NC ? c + 1 : 0;
+#pragma unroll
+                for (int u = 0; u < UT; ++u) xn[u] = operand(tn, UT * cn + u);
+                if (c == 0) wn = make((t + 1) & 15);
+#pragma unroll
+                for (int u = 0; u < UT; ++u)
+                    acc[UT * c + u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(xa[u], wb, acc[UT * c + u], 0, 0, 0);
+#pragma unroll
+                for (int u = 0; u < UT; ++u) xa[u] = xn[u];
+            }
+            wb = wn;
+            // the order of a step: the next operands first, then matrix instructions with look-ups between them
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                __builtin_amdgcn_sched_group_barrier(0x100, UT, 0);
+#pragma unroll
+                for (int u = 0; u < UT; ++u) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, kBetween<QT>, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            // what the step before the last barrier asked for has landed; what this stage asked for is still under way
+            if ((t & 3) == 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XU) : "memory");
+        }
+    }
+
+    if constexpr (TEAMS > 1) {
+        // the other teams hand their accumulators over through the tiles, once no load into them is under way
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        v4f *xchg = reinterpret_cast<v4f *>(lds);
+        constexpr int NV = QT * 4;            // 16-byte vectors per lane
+        if (team > 0) {
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    xchg[(((team - 1) * SW + tw) * NV + q * 4 + e) * 64 + lane] =
+                        v4f{acc[q][4 * e], acc[q][4 * e + 1], acc[q][4 * e + 2], acc[q][4 * e + 3]};
+        }
+        __syncthreads();
+        if (team > 0) return;
+#pragma unroll
+        for (int k = 1; k < TEAMS; ++k)
+#pragma unroll
+            for (int q = 0; q < QT; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const v4f v = xchg[(((k - 1) * SW + tw) * NV + q * 4 + e) * 64 + lane];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[q][4 * e + i] += v[i];
+                }
+    }
+
+    // element e of a tile: request 8 (e / 4) + 4 half + e % 4 of row r32
+    const uint32_t row = row0 + r32;
+    if (row < a.m) {
+#pragma unroll
+        for (int q = 0; q < QT; ++q)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int r = 32 * (wq * QT + q) + 8 * (e / 4) + 4 * half + (e % 4);
+                if (r < nreq) a.y[(size_t)(BYCLASS ? req_of[r] : (uint32_t)(b0 + r)) * a.m + row] = (_Float16)acc[q][e];
+            }
+    }
+}
+
+template <int P, typename S, bool OFFSET>
+__global__ __launch_bounds__(S::THREADS) void level_mfma_kernel(LevelParams a)
+{
+    uint32_t wg = blockIdx.x;
+    if (a.nmat > 1) {
+        // which matrix this row of workgroups belongs to, picked by comparison (no indexing of the arguments)
+        static_assert(BCQ_MAX_MULTI == 4, "the selection below is written for four matrices");
+        const bool g1 = wg >= a.mat_blk0[1], g2 = wg >= a.mat_blk0[2], g3 = wg >= a.mat_blk0[3];
+        a.planes = g3 ? a.mat_planes[3] : g2 ? a.mat_planes[2] : g1 ? a.mat_planes[1] : a.mat_planes[0];
+        a.scales = g3 ? a.mat_scales[3] : g2 ? a.mat_scales[2] : g1 ? a.mat_scales[1] : a.mat_scales[0];
+        a.y = g3 ? a.mat_y[3] : g2 ? a.mat_y[2] : g1 ? a.mat_y[1] : a.mat_y[0];
+        a.m = g3 ? a.mat_m[3] : g2 ? a.mat_m[2] : g1 ? a.mat_m[1] : a.mat_m[0];
+        wg -= g3 ? a.mat_blk0[3] : g2 ? a.mat_blk0[2] : g1 ? a.mat_blk0[1] : 0u;
+        a.plane_stride = a.m * a.row_stride;
+        a.scale_plane_stride = a.m * a.scale_row_stride;
+    }
+    const int b0 = (int)blockIdx.y * S::REQS;
+    level_body<P, S, OFFSET, false>(a, b0, min(S::REQS, a.batch - b0), nullptr, wg);
+}
+
+template <int P, typename S, bool OFFSET>
+hipError_t launch(LevelParams pr, hipStream_t stream)
+{
+    auto kernel = level_mfma_kernel<P, S, OFFSET>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), S::LDS)) return e;
+    uint32_t wgs = (pr.m + S::ROWS - 1) / S::ROWS;
+    if (pr.nmat > 1) {
+        // every matrix gets whole workgroups
+        wgs = 0;
+        for (int k = 0; k < BCQ_MAX_MULTI; ++k) {
+            pr.mat_blk0[k] = wgs;
+            if (k < pr.nmat) wgs += (pr.mat_m[k] + S::ROWS - 1) / S::ROWS;
+        }
+        for (int k = pr.nmat; k < BCQ_MAX_MULTI; ++k) pr.mat_blk0[k] = wgs;      // never reached
+    }
+    hipLaunchKernelGGL(kernel, dim3(wgs, (unsigned)((pr.batch + S::REQS - 1) / S::REQS)), dim3(S::THREADS), S::LDS, stream, pr);
+    return hipGetLastError();
+}
+
+template <typename S>
+hipError_t launch_shape(const LevelParams &pr, int p, bool offset, hipStream_t stream)
+{
+    switch (p) {
+    case 1: return offset ? launch<1, S, true>(pr, stream) : launch<1, S, false>(pr, stream);
+    case 2: return offset ? launch<2, S, true>(pr, stream) : launch<2, S, false>(pr, stream);
+    case 3: return offset ? launch<3, S, true>(pr, stream) : launch<3, S, false>(pr, stream);
+    default: return offset ? launch<4, S, true>(pr, stream) : launch<4, S, false>(pr, stream);
+    }
+}
+
+// Shapes and what a grid of each costs: microseconds per 128 columns with 256 and with 128 workgroups on the chip (n = 4096),
+// p = 4 and p = 2.  Their LDS allows one workgroup per CU, so a call costs its rounds of workgroups over the 256 CUs; a
+// round that fills half of the chip is quicker by up to a third, because with random operands the full one is held back by
+// power (256 x 256, p = 2, per pair of groups: 7.6 us on 256 CUs, 5.6 on 128, and 5.3 on 256 with activations of zero).
+// The costs are compared with those of the other form (cheapest_shape).  Large tiles rebuild a weight for more requests, small
+// ones keep the CUs busy on short matrices and batches.
+struct LevelShape {
+    int rows, reqs;
+    float full_p4, full_p2, half_p4, half_p2;
+};
+constexpr LevelShape kLevelShapes[] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f},
+                                       {128, 128, 1.62f, 1.34f, 1.43f, 1.06f}, {64, 128, 1.07f, 0.97f, 0.92f, 0.81f},
+                                       {128, 64, 1.11f, 0.82f, 1.00f, 0.72f},  {64, 64, 0.69f, 0.56f, 0.67f, 0.47f}};
+constexpr int kLevelShapeCount = 6;
+thread_local int g_forced_shape = -1;
+
+}  // namespace
+
+bool level_mfma_force_shape(int shape)
+{
+    if (shape >= kLevelShapeCount) return false;
+    g_forced_shape = shape;
+    return true;
+}
+
+int level_mfma_forced_shape() { return g_forced_shape; }
+
+// whole pairs of 128-column groups; 32-bit byte offsets are the caller's condition (dequant_mfma_supports)
+bool level_mfma_supports(const GemmArgs &a) { return a.uniform_p >= 1 && a.uniform_p <= kMaxP && a.n % 256 == 0; }
+
+int level_mfma_cheapest(int p, int64_t m, int batch, int times, float &cost)
+{
+    int best = -1;
+    for (int k = 0; k < kLevelShapeCount; ++k) {
+        const LevelShape &c = kLevelShapes[k];
+        const float wgs = (float)((m + c.rows - 1) / c.rows) * (float)((batch + c.reqs - 1) / c.reqs) * (float)times;
+        const float full = p >= 3 ? c.full_p4 : c.full_p2, half = p >= 3 ? c.half_p4 : c.half_p2;
+        const float rounds = __builtin_floorf(wgs / 256.f), rest = wgs / 256.f - rounds;
+        const float all = rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f));
+        if (best < 0 || all < cost) {
+            best = k;
+            cost = all;
+        }
+    }
+    return best;
+}
+
+hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count)
+{
+    LevelParams pr{};
+    pr.planes = reinterpret_cast<const unsigned char *>(a.planes);
+    pr.x = reinterpret_cast<const unsigned char *>(a.x);
+    pr.y = a.y;
+    pr.plane_stride = (uint32_t)(a.m * (a.n / 8));
+    pr.row_stride = (uint32_t)(a.n / 8);
+    pr.scale_plane_stride = (uint32_t)(a.m * (a.n / a.group) * 2);
+    pr.scale_row_stride = (uint32_t)((a.n / a.group) * 2);
+    pr.gshift = a.group == 256 ? 1 : a.group == 64 ? -1 : 0;
+    pr.x_stride = (uint32_t)(a.n * 2);
+    pr.m = (uint32_t)a.m;
+    pr.batch = a.batch;
+    pr.npairs = (int)(a.n / 256);
+    pr.scales = reinterpret_cast<const unsigned char *>(a.scales[a.uniform_p]);
+    const bool offset = a.offsets[a.uniform_p] != nullptr;
+    pr.offsets = reinterpret_cast<const unsigned char *>(a.offsets[a.uniform_p]);
+    if (mats && count > 1) {
+        pr.nmat = count;
+        for (int k = 0; k < count; ++k) {
+            pr.mat_planes[k] = reinterpret_cast<const unsigned char *>(mats[k].planes);
+            pr.mat_scales[k] = reinterpret_cast<const unsigned char *>(mats[k].scales[a.uniform_p]);
+            pr.mat_y[k] = mats[k].y;
+            pr.mat_m[k] = (uint32_t)mats[k].m;
+        }
+    }
+    switch (shape) {
+    case 0: return launch_shape<Shape<8, 8, 1, 1>>(pr, a.uniform_p, offset, stream);
+    case 1: return launch_shape<Shape<4, 4, 2, 1>>(pr, a.uniform_p, offset, stream);
+    case 2: return launch_shape<Shape<4, 4, 1, 2>>(pr, a.uniform_p, offset, stream);
+    case 3: return launch_shape<Shape<4, 2, 1, 2>>(pr, a.uniform_p, offset, stream);
+    case 4: return launch_shape<Shape<2, 4, 1, 2>>(pr, a.uniform_p, offset, stream);
+    case 5: return launch_shape<Shape<2, 2, 1, 4>>(pr, a.uniform_p, offset, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace bcq

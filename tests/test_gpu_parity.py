@@ -694,6 +694,57 @@ def test_seeded_random_cases_against_the_oracle(gpu):
         done += 1
 
 
+# rows x requests of the level form's shapes, in the order of their codes 100 .. 105
+LEVEL_TILES = [(256, 256), (128, 256), (128, 128), (64, 128), (128, 64), (64, 64)]
+
+
+@pytest.mark.parametrize("code", range(6))
+@pytest.mark.parametrize("n,group", [(256, 128), (768, 64), (1280, 128), (2560, 256)])
+def test_level_form_edges(gpu, forced_shape, code, n, group):
+    """The look-up form of the large-batch kernel at the edges of its tiles (one request, one under, one over; one row over and
+    a short block), with one pair of column groups (fewer than there are teams), three, five and ten, at every depth, with
+    and without offsets.  Tolerance: that of every product (the weights are those of the summing form)."""
+    rows, reqs = LEVEL_TILES[code]
+    forced_shape(f"1,{100 + code}")
+    for m, batch in ((rows + 1, reqs - 1), (21, reqs + 1), (rows, 1)):
+        layer = syn.make_layer(m, n, group=group, seed=(930, m, n), signed=True)
+        dl = gpu.DeviceLayer(layer)
+        x = syn.make_x(batch, n, seed=(931, batch))
+        for p in (1, 2, 3, 4):
+            for offsets in (None, syn.make_offsets(p, m, n, group, seed=(932, m, p))):
+                used, _ = gpu.check_gemv(dl, p, x, "dequant_mfma", group, offsets=offsets)
+                assert used == "dequant_mfma"
+
+
+def test_level_form_several_matrices_and_unsupported_width(gpu, oracle, forced_shape):
+    """Several matrices whose rows fill no workgroup evenly in one launch; a width that is not whole pairs of groups is refused
+    when the form is forced and runs otherwise."""
+    import torch
+
+    import paper_2510_10467_amd as bcq
+    n, batch = 512, 70
+    layers = [syn.make_layer(m, n, seed=(933, m), signed=True) for m in (150, 70, 33, 260)]
+    dls = [gpu.DeviceLayer(layer) for layer in layers]
+    xh = syn.make_x(batch, n, seed=(933, 0))
+    odd = gpu.DeviceLayer(syn.make_layer(40, 640, seed=(934, 0)))
+    x_odd = syn.make_x(batch, 640, seed=(934, 0))
+    for code in range(6):
+        forced_shape(f"1,{100 + code}")
+        bcq.select_kernel("dequant_mfma")
+        try:
+            with pytest.raises(bcq.BcqError):
+                bcq.bcq_gemv(odd.planes, odd.scales[3], 3, gpu.to_dev(x_odd))
+            ys = bcq.bcq_gemv_multi([d.planes for d in dls], [d.scales[3] for d in dls], 3, gpu.to_dev(xh))
+            torch.cuda.synchronize()
+        finally:
+            bcq.select_kernel("auto")
+        for d, y in zip(dls, ys):
+            y_ref, a_ref = oracle.gemv(d.layer.planes, d.layer.scales[3], xh)
+            gpu.assert_within_tolerance(y, y_ref, a_ref, f"level form {code} with several matrices")
+    bcq.select_dequant_shape(0, 0)
+    gpu.check_gemv(odd, 3, x_odd, "dequant_mfma")
+
+
 def test_seeded_random_cases_on_the_table_look_up_kernel(gpu):
     """Forty seeded random cases forced onto the table look-ups: widths that are multiples of 32 only (one to four table
     tiles, ragged last tile), groups of 32 to 416 columns, planes stored to 3..8, ragged row counts on both sides of the
