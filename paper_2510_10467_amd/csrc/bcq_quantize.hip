@@ -51,19 +51,27 @@ __device__ __forceinline__ double flip(double v, uint32_t sign_mask)   // sign_m
 // 0x80000000 where column j of the word is -1 (bit clear); nw is the complemented word
 __device__ __forceinline__ uint32_t minus_mask(uint32_t nw, int j) { return (nw << (31 - j)) & 0x80000000u; }
 
-template <int LANES>
-__device__ __forceinline__ double group_sum(double v)
+// Sums over the LANES adjacent lanes of a group, in all of them: pairs, quads, eights.  The exchanges are row permutes of the
+// vector unit (lane ^ 1, lane ^ 2, and lane 7 - i of eight, which holds the sum of the other quad) and not reads through the
+// LDS crossbar, whose latency every cycle would wait for several times (4096 x 4096, p = 2 .. 4, T = 20: 271 -> 245 us; 315 x
+// 3840 in groups of 256 with offsets, p = 2 .. 3, T = 7, few waves: 28.7 -> 23.7).
+template <int CTRL>
+__device__ __forceinline__ int from_lane(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true); }
+
+template <int CTRL>
+__device__ __forceinline__ double from_lane(double v)
 {
-#pragma unroll
-    for (int mask = 1; mask < LANES; mask <<= 1) v += __shfl_xor(v, mask, 64);
-    return v;
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)from_lane<CTRL>((int)(uint32_t)u), hi = (uint32_t)from_lane<CTRL>((int)(uint32_t)(u >> 32));
+    return __builtin_bit_cast(double, (uint64_t)lo | ((uint64_t)hi << 32));
 }
 
-template <int LANES>
-__device__ __forceinline__ int group_sum(int v)
+template <int LANES, typename T>
+__device__ __forceinline__ T group_sum(T v)
 {
-#pragma unroll
-    for (int mask = 1; mask < LANES; mask <<= 1) v += __shfl_xor(v, mask, 64);
+    if constexpr (LANES >= 2) v += from_lane<0xB1>(v);
+    if constexpr (LANES >= 4) v += from_lane<0x4E>(v);
+    if constexpr (LANES >= 8) v += from_lane<0x141>(v);
     return v;
 }
 
@@ -81,19 +89,41 @@ __device__ __forceinline__ _Float16 to_half(double d)
     return (_Float16)f;
 }
 
+// Division by one number several times: its reciprocal to full precision once (two Newton steps), then per quotient an estimate
+// and one correction by the exact remainder (Markstein), which is the correctly rounded quotient for the operands here:
+// a divisor above 1e-9 and at most 256, and dividends that are zero or far from the ends of the exponent range.  DIV_FIXUP
+// gives infinities and NaN what a division gives them.  (With the kernel of its own for base precision 2, 294 -> 271 us.)
+struct Divisor {
+    double d, inv;
+    __device__ __forceinline__ void set(double v)
+    {
+        d = v;
+        double y = __builtin_amdgcn_rcp(v);
+        y = __builtin_fma(y, __builtin_fma(-v, y, 1.0), y);
+        inv = __builtin_fma(y, __builtin_fma(-v, y, 1.0), y);
+    }
+    __device__ __forceinline__ double under(double a) const
+    {
+        const double q = a * inv;
+        return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-d, q, a), inv, q), d, a);
+    }
+};
+
 // Least squares through the normal equations, eliminated in order without pivoting.
 // A is the full symmetric Gram matrix on entry.
 template <int K>
 __device__ __forceinline__ void solve(double (&A)[K][K], double (&rhs)[K], double (&coef)[K])
 {
     bool dead[K];
+    Divisor pivot[K];                         // (the first pivot is the group size, a power of two known to the compiler)
 #pragma unroll
     for (int c = 0; c < K; ++c) {
         dead[c] = !(A[c][c] > 1e-9);
         if (!dead[c]) {
+            if (c > 0) pivot[c].set(A[c][c]);
 #pragma unroll
             for (int r = c + 1; r < K; ++r) {
-                const double f = A[r][c] / A[c][c];
+                const double f = c > 0 ? pivot[c].under(A[r][c]) : A[r][c] / A[c][c];
 #pragma unroll
                 for (int d = c + 1; d < K; ++d) A[r][d] = A[r][d] - f * A[c][d];
                 rhs[r] = rhs[r] - f * rhs[c];
@@ -109,7 +139,7 @@ __device__ __forceinline__ void solve(double (&A)[K][K], double (&rhs)[K], doubl
 #pragma unroll
             for (int d = c + 1; d < K; ++d)
                 if (!dead[d]) s = s - A[c][d] * coef[d];
-            coef[c] = s / A[c][c];
+            coef[c] = c > 0 ? pivot[c].under(s) : s / A[c][c];
         }
     }
 }
@@ -191,7 +221,7 @@ __device__ __forceinline__ void greedy_plane(Lane &s)
 // The alternation stops early at a fixed point: a cycle is a function of the codes alone, so codes that come
 // out as they went in give the same scales and the same codes in every cycle that is left.  The lanes of a wave go on
 // together until none of their groups has changed a code (groups that have settled repeat themselves).  Normal weights
-// with a few outliers settle in a fraction of 20 cycles (4096 x 4096, p = 2 .. 4, T = 20: 446.5 -> 294.4 us).
+// with a few outliers settle in a fraction of 20 cycles (4096 x 4096, p = 2 .. 4, T = 20: 446 -> 294 us).
 template <int P>
 __device__ __forceinline__ bool any_changed(const Lane &s, const uint32_t (&word)[P])
 {
@@ -275,11 +305,12 @@ __device__ __forceinline__ void base_stage_two(Lane &s, int cycles, double sum_w
             acc0[j & 1] += top ? wj : -wj;
             acc1[j & 1] += low ? wj : -wj;
         }
-        if (!any_changed<2>(s, word)) break;
+        const bool changed = any_changed<2>(s, word);
         s.word[0] = word[0];
         s.word[1] = word[1];
         rhs_w[0] = group_sum<LANES>(acc0[0] + acc0[1]);
         rhs_w[1] = group_sum<LANES>(acc1[0] + acc1[1]);
+        if (!changed) break;
     }
 }
 
@@ -358,7 +389,9 @@ __device__ __forceinline__ void store_set(const QuantParams &a, const Lane &s, i
     if constexpr (OFFSET) a.offsets[p][gid] = to_half(s.z);
 }
 
-template <int LANES, bool OFFSET, bool LISTING>
+// TWO: base precision 2, the one of the paper's experiments; a kernel of its own keeps the registers of the other base stages
+// (sixteen levels in double precision) out of it.
+template <int LANES, bool OFFSET, bool LISTING, bool TWO>
 __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
 {
     __shared__ double tables[(256 / LANES) * 8];
@@ -389,23 +422,26 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
     sum_w = group_sum<LANES>(sum_w);
     if constexpr (OFFSET) s.z = sum_w / (32.0 * LANES);
 
-    const int p_low = a.p_low;
+    const int p_low = TWO ? 2 : a.p_low;
     greedy_plane<0, LANES, OFFSET>(s);
     if (p_low > 1) greedy_plane<1, LANES, OFFSET>(s);
     if (p_low > 2) greedy_plane<2, LANES, OFFSET>(s);
     if (p_low > 3) greedy_plane<3, LANES, OFFSET>(s);
-    switch (p_low) {
-    case 1: base_stage<1, LANES, OFFSET>(s, a.cycles, sum_w); break;
-    case 2: base_stage_two<LANES, OFFSET>(s, a.cycles, sum_w); break;
-    case 3: base_stage<3, LANES, OFFSET>(s, a.cycles, sum_w); break;
-    default: base_stage<4, LANES, OFFSET>(s, a.cycles, sum_w); break;
+    if constexpr (TWO) {
+        base_stage_two<LANES, OFFSET>(s, a.cycles, sum_w);
+    } else {
+        switch (p_low) {
+        case 1: base_stage<1, LANES, OFFSET>(s, a.cycles, sum_w); break;
+        case 3: base_stage<3, LANES, OFFSET>(s, a.cycles, sum_w); break;
+        default: base_stage<4, LANES, OFFSET>(s, a.cycles, sum_w); break;
+        }
     }
     const uint64_t gid = gw / LANES;
     const bool writer = valid && (threadIdx.x % LANES) == 0;
     store_set<LANES, OFFSET>(a, s, p_low, gid, writer);
     for (int p = p_low + 1; p <= a.p_high; ++p) {
         switch (p) {
-        case 2: expand_stage<2, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
+        case 2: if constexpr (!TWO) expand_stage<2, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
         case 3: expand_stage<3, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
         default: expand_stage<4, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
         }
@@ -418,18 +454,24 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
     }
 }
 
-template <int LANES>
+template <int LANES, bool TWO>
 hipError_t launch_lanes(const QuantParams &pr, bool offset, bool listing, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((pr.total_words + 255) / 256);
     if (listing) {
-        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, true>), dim3(blocks), dim3(256), 0, stream, pr);
-        else hipLaunchKernelGGL((quantize_kernel<LANES, false, true>), dim3(blocks), dim3(256), 0, stream, pr);
+        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, true, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
+        else hipLaunchKernelGGL((quantize_kernel<LANES, false, true, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
     } else {
-        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, false>), dim3(blocks), dim3(256), 0, stream, pr);
-        else hipLaunchKernelGGL((quantize_kernel<LANES, false, false>), dim3(blocks), dim3(256), 0, stream, pr);
+        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, false, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
+        else hipLaunchKernelGGL((quantize_kernel<LANES, false, false, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
     }
     return hipGetLastError();
+}
+
+template <int LANES>
+hipError_t launch_lanes(const QuantParams &pr, bool offset, bool listing, hipStream_t stream)
+{
+    return pr.p_low == 2 ? launch_lanes<LANES, true>(pr, offset, listing, stream) : launch_lanes<LANES, false>(pr, offset, listing, stream);
 }
 
 }  // namespace
