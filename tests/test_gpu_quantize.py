@@ -69,6 +69,21 @@ def test_precision_ranges(p_low, p_high, cycles):
     compare(syn.make_weights(48, 512, seed=(92, p_low * 10 + p_high)), p_low, p_high, cycles)
 
 
+@pytest.mark.parametrize("group", [32, 64, 128, 256])
+@pytest.mark.parametrize("cycles", [1, 2, 40])
+@pytest.mark.parametrize("with_offset,listing", [(False, False), (True, True)])
+def test_groups_that_settle_and_groups_that_do_not(group, cycles, with_offset, listing):
+    """A wave stops cycling once none of its groups changes a code: waves whose groups all settle at once (constant, zero and
+    two-valued rows, where pivots vanish too), waves that mix these with slow ones, fewer and more cycles than they need."""
+    w = syn.make_weights(24, 1024, seed=(96, group, cycles))
+    w[0] = 0.0
+    w[1] = 0.25
+    w[2, ::2], w[2, 1::2] = -0.5, 0.5
+    w[3, :512] = 0.0
+    for p_low in (1, 2, 3):
+        compare(w, p_low, 4, cycles, group=group, with_offset=with_offset, listing=listing)
+
+
 @pytest.mark.parametrize("group", [32, 64, 256])
 def test_group_sizes(group):
     compare(syn.make_weights(24, 1024, seed=(93, group)), 2, 4, 6, group=group)
