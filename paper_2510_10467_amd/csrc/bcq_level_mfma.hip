@@ -10,7 +10,7 @@
 //                     plane 3 is -1 and the sign goes onto the high byte
 //   p = 4, offsets    sixteen levels, two look-ups per byte and a select
 //
-// The product runs on v_mfma_f32_32x32x16_f16: a wave owns RT tiles of 32 rows and QT tiles of 32 requests.  Against 16 x 16
+// The product runs on v_mfma_f32_32x32x16_f16: a wave owns one tile of 32 rows and QT tiles of 32 requests.  Against 16 x 16
 // tiles an instruction needs half as many operand reads from LDS per operation, and it leaves the SIMD's issue slots free for
 // half of its 32 cycles, which is where the look-ups go.  The two lane halves hold the two 128-column groups of a pair
 // of groups (a permutation of K which the activations follow), so that a lane sees one group and one set of levels:
@@ -60,12 +60,6 @@ struct LevelParams {
     uint32_t m;
     int batch, npairs;                      // npairs: pairs of 128-column groups
     int gshift;                             // scale groups of 64 (-1), 128 (0) or 256 (+1) columns
-    // per-request precision: a scale / offset set per precision, nullptr where there is none
-    const unsigned char *scale_sets[kMaxP + 1];
-    const unsigned char *offset_sets[kMaxP + 1];
-    const int32_t *p_req;
-    int p_max;
-    uint32_t class_order;                   // byte y = the precision served by the workgroups with blockIdx.y = y
     // several matrices in one launch (nmat > 1): matrix k owns the workgroup rows mat_blk0[k] .. mat_blk0[k+1]-1
     int nmat;
     const unsigned char *mat_planes[BCQ_MAX_MULTI];
@@ -206,12 +200,12 @@ struct Shape {
     static constexpr int LDS = TEAMS * kRing * TILE;
     static_assert(XU * 1024 * SW == TILE && XU >= 1, "tile does not split over the team");
     static_assert((TEAMS - 1) * SW * QT * 4096 <= LDS, "accumulator exchange must fit in the tiles");
-    static_assert(LDS + REQS * 4 <= 160 * 1024, "tiles and request numbers must fit in LDS");
+    static_assert(LDS <= 160 * 1024, "tiles must fit in LDS");
 };
 
-// BYCLASS: the workgroup serves `nreq` requests whose numbers are in req_of (LDS); otherwise requests b0 .. of the batch.
-template <int P, typename S, bool OFFSET, bool BYCLASS>
-__device__ __forceinline__ void level_body(const LevelParams &a, const int b0, const int nreq, const uint32_t *req_of, const uint32_t rowblk)
+// the workgroup's rows (block rowblk of the matrix) and requests b0 .. b0 + nreq - 1
+template <int P, typename S, bool OFFSET>
+__device__ __forceinline__ void level_body(const LevelParams &a, const int b0, const int nreq, const uint32_t rowblk)
 {
     constexpr int QT = S::QT, TEAMS = S::TEAMS, XU = S::XU, SW = S::SW;
     constexpr int UT = QT < 4 ? QT : 4;       // request tiles whose operands are held at a time
@@ -238,7 +232,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
     for (int k = 0; k < XU; ++k) {
         const int req = 8 * (k * SW + tw) + (lane >> 3);
         const int part = (lane & 7) ^ ((req >> 1) & 7);
-        const uint32_t source = BYCLASS ? req_of[min(req, nreq - 1)] : (uint32_t)(b0 + min(req, nreq - 1));
+        const uint32_t source = (uint32_t)(b0 + min(req, nreq - 1));
         xs_src[k] = source * a.x_stride + (part >> 2) * 256 + (part & 3) * 16;
     }
     // (buffer loads: the compiler counts loads of the global kind that write LDS among the LDS reads under way as well, and
@@ -407,7 +401,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int r = 32 * (wq * QT + q) + 8 * (e / 4) + 4 * half + (e % 4);
-                if (r < nreq) a.y[(size_t)(BYCLASS ? req_of[r] : (uint32_t)(b0 + r)) * a.m + row] = (_Float16)acc[q][e];
+                if (r < nreq) a.y[(size_t)(b0 + r) * a.m + row] = (_Float16)acc[q][e];
             }
     }
 }
@@ -429,7 +423,7 @@ __global__ __launch_bounds__(S::THREADS) void level_mfma_kernel(LevelParams a)
         a.scale_plane_stride = a.m * a.scale_row_stride;
     }
     const int b0 = (int)blockIdx.y * S::REQS;
-    level_body<P, S, OFFSET, false>(a, b0, min(S::REQS, a.batch - b0), nullptr, wg);
+    level_body<P, S, OFFSET>(a, b0, min(S::REQS, a.batch - b0), wg);
 }
 
 template <int P, typename S, bool OFFSET>
