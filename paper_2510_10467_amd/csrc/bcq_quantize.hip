@@ -38,7 +38,7 @@ struct QuantParams {
     _Float16 *offsets[kMaxP + 1];        // [p]: [total_groups]
     uint64_t total_words;                // m * n / 32
     uint64_t total_groups;               // m * n / group
-    int p_low, p_high, cycles;
+    int p_high, cycles;
 };
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -370,11 +370,14 @@ __device__ __forceinline__ void expand_stage(Lane &s, int cycles, double sum_w, 
             acc[j & 1] += flip(s.w[j], rhi & 0x80000000u);
         }
         __builtin_amdgcn_wave_barrier();
-        // (the first cycle starts from codes that were never chosen: nothing to compare with)
-        if (t > 0 && __ballot(~minus != own) == 0) break;
+        // (asked before the solve, acted on after it: a branch here keeps the sums below from overlapping with the columns,
+        // 2048 x 4096 in groups of 128, p = 1 .. 4, T = 1: 25.1 against 23.3 us)
+        const bool changed = __ballot(~minus != own) != 0;
         s.word[P - 1] = ~minus;
         rhs_w[P - 1] = group_sum<LANES>(acc[0] + acc[1]);
         least_squares<P, LANES, OFFSET>(s, rhs_w, sum_w);
+        // (the first cycle starts from codes that were never chosen: nothing to compare with)
+        if (t > 0 && !changed) break;
     }
 }
 
@@ -389,9 +392,12 @@ __device__ __forceinline__ void store_set(const QuantParams &a, const Lane &s, i
     if constexpr (OFFSET) a.offsets[p][gid] = to_half(s.z);
 }
 
-// TWO: base precision 2, the one of the paper's experiments; a kernel of its own keeps the registers of the other base stages
-// (sixteen levels in double precision) out of it.
-template <int LANES, bool OFFSET, bool LISTING, bool TWO>
+// LOW: the base precision, a kernel for each, and the stages one after another in straight line.  With base precisions 1, 3 and 4
+// in one kernel, or with the expansions in a loop over p (out of which the compiler moves what depends on the first planes alone,
+// some forty registers of look-up addresses that then live through every stage), the forms with offsets need more than
+// the 256 registers that let two waves share a SIMD.  2048 x 4096 in groups of 128 with offsets, T = 7, one wave per SIMD and now:
+// p = 1 .. 4 119.5 -> 90.4 us, 3 .. 4 177.9 -> 140.4, 4 alone 253.1 -> 201.6.
+template <int LANES, bool OFFSET, bool LISTING, int LOW>
 __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
 {
     __shared__ double tables[(256 / LANES) * 8];
@@ -422,30 +428,32 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
     sum_w = group_sum<LANES>(sum_w);
     if constexpr (OFFSET) s.z = sum_w / (32.0 * LANES);
 
-    const int p_low = TWO ? 2 : a.p_low;
     greedy_plane<0, LANES, OFFSET>(s);
-    if (p_low > 1) greedy_plane<1, LANES, OFFSET>(s);
-    if (p_low > 2) greedy_plane<2, LANES, OFFSET>(s);
-    if (p_low > 3) greedy_plane<3, LANES, OFFSET>(s);
-    if constexpr (TWO) {
-        base_stage_two<LANES, OFFSET>(s, a.cycles, sum_w);
-    } else {
-        switch (p_low) {
-        case 1: base_stage<1, LANES, OFFSET>(s, a.cycles, sum_w); break;
-        case 3: base_stage<3, LANES, OFFSET>(s, a.cycles, sum_w); break;
-        default: base_stage<4, LANES, OFFSET>(s, a.cycles, sum_w); break;
-        }
-    }
+    if constexpr (LOW > 1) greedy_plane<1, LANES, OFFSET>(s);
+    if constexpr (LOW > 2) greedy_plane<2, LANES, OFFSET>(s);
+    if constexpr (LOW > 3) greedy_plane<3, LANES, OFFSET>(s);
+    if constexpr (LOW == 2) base_stage_two<LANES, OFFSET>(s, a.cycles, sum_w);
+    else base_stage<LOW, LANES, OFFSET>(s, a.cycles, sum_w);
     const uint64_t gid = gw / LANES;
     const bool writer = valid && (threadIdx.x % LANES) == 0;
-    store_set<LANES, OFFSET>(a, s, p_low, gid, writer);
-    for (int p = p_low + 1; p <= a.p_high; ++p) {
-        switch (p) {
-        case 2: if constexpr (!TWO) expand_stage<2, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
-        case 3: expand_stage<3, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
-        default: expand_stage<4, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group); break;
+    store_set<LANES, OFFSET>(a, s, LOW, gid, writer);
+    if constexpr (LOW < 2) {
+        if (a.p_high >= 2) {
+            expand_stage<2, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group);
+            store_set<LANES, OFFSET>(a, s, 2, gid, writer);
         }
-        store_set<LANES, OFFSET>(a, s, p, gid, writer);
+    }
+    if constexpr (LOW < 3) {
+        if (a.p_high >= 3) {
+            expand_stage<3, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group);
+            store_set<LANES, OFFSET>(a, s, 3, gid, writer);
+        }
+    }
+    if constexpr (LOW < 4) {
+        if (a.p_high >= 4) {
+            expand_stage<4, LANES, OFFSET, LISTING>(s, a.cycles, sum_w, table, lane_in_group);
+            store_set<LANES, OFFSET>(a, s, 4, gid, writer);
+        }
     }
     if (valid) {
 #pragma unroll
@@ -454,24 +462,31 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams a)
     }
 }
 
-template <int LANES, bool TWO>
-hipError_t launch_lanes(const QuantParams &pr, bool offset, bool listing, hipStream_t stream)
+template <int LANES, int LOW>
+hipError_t launch_low(const QuantParams &pr, bool offset, bool listing, hipStream_t stream)
 {
     const unsigned blocks = (unsigned)((pr.total_words + 255) / 256);
-    if (listing) {
-        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, true, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
-        else hipLaunchKernelGGL((quantize_kernel<LANES, false, true, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
-    } else {
-        if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, false, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
-        else hipLaunchKernelGGL((quantize_kernel<LANES, false, false, TWO>), dim3(blocks), dim3(256), 0, stream, pr);
+    if constexpr (LOW < kMaxP) {              // (without an expansion there is no residual to choose)
+        if (listing) {
+            if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, true, LOW>), dim3(blocks), dim3(256), 0, stream, pr);
+            else hipLaunchKernelGGL((quantize_kernel<LANES, false, true, LOW>), dim3(blocks), dim3(256), 0, stream, pr);
+            return hipGetLastError();
+        }
     }
+    if (offset) hipLaunchKernelGGL((quantize_kernel<LANES, true, false, LOW>), dim3(blocks), dim3(256), 0, stream, pr);
+    else hipLaunchKernelGGL((quantize_kernel<LANES, false, false, LOW>), dim3(blocks), dim3(256), 0, stream, pr);
     return hipGetLastError();
 }
 
 template <int LANES>
-hipError_t launch_lanes(const QuantParams &pr, bool offset, bool listing, hipStream_t stream)
+hipError_t launch_lanes(const QuantParams &pr, int p_low, bool offset, bool listing, hipStream_t stream)
 {
-    return pr.p_low == 2 ? launch_lanes<LANES, true>(pr, offset, listing, stream) : launch_lanes<LANES, false>(pr, offset, listing, stream);
+    switch (p_low) {
+    case 1: return launch_low<LANES, 1>(pr, offset, listing, stream);
+    case 2: return launch_low<LANES, 2>(pr, offset, listing, stream);
+    case 3: return launch_low<LANES, 3>(pr, offset, listing, stream);
+    default: return launch_low<LANES, 4>(pr, offset, listing, stream);
+    }
 }
 
 }  // namespace
@@ -495,15 +510,14 @@ hipError_t quantize_launch(const _Float16 *w, int p_low, int p_high, int cycles,
     }
     pr.total_words = (uint64_t)(m * n / 32);
     pr.total_groups = (uint64_t)(m * n / group);
-    pr.p_low = p_low;
     pr.p_high = p_high;
     pr.cycles = cycles;
     const bool offset = offsets_by_p != nullptr;
     switch (group) {
-    case 32: return launch_lanes<1>(pr, offset, listing_residual, stream);
-    case 64: return launch_lanes<2>(pr, offset, listing_residual, stream);
-    case 128: return launch_lanes<4>(pr, offset, listing_residual, stream);
-    default: return launch_lanes<8>(pr, offset, listing_residual, stream);
+    case 32: return launch_lanes<1>(pr, p_low, offset, listing_residual, stream);
+    case 64: return launch_lanes<2>(pr, p_low, offset, listing_residual, stream);
+    case 128: return launch_lanes<4>(pr, p_low, offset, listing_residual, stream);
+    default: return launch_lanes<8>(pr, p_low, offset, listing_residual, stream);
     }
 }
 
