@@ -56,6 +56,14 @@ int bcq_selected_kernel(void);
  */
 int bcq_select_dequant_shape(int request_tiles, int row_blocks);
 
+/*
+ * The workgroup shape, as a pair of bcq_select_dequant_shape, that BCQ_KERNEL_DEQUANT_MFMA runs a product of this size at
+ * precision p with: the calling thread's forced one, or the automatic choice ((1, 100) and above: the level form).  The matrices
+ * of one bcq_gemv_multi count as one of all their rows.  Needs no GPU.  Returns 0, -1 NULL, or -6 if that kernel does not take
+ * the problem.
+ */
+int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks);
+
 /* Name of the variant the calling thread's most recent successful launch used ("" before any): "sign_select",
  * "lut", "plane_mfma" ("plane_mfma_rows" where that family ran in its row-streaming form: tall matrices with two to eight
  * requests, or with one request at one or two planes), "dequant_mfma", "plane_f16", "quantize". */

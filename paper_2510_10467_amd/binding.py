@@ -43,6 +43,8 @@ def lib() -> ctypes.CDLL:
         L.bcq_select_dequant_shape.argtypes = [i32, i32]
         L.bcq_select_dequant_shape.restype = i32
         L.bcq_last_kernel.restype = ctypes.c_char_p
+        L.bcq_dequant_shape_for.argtypes = [i32, i64, i64, i32, i32, i32, vp, vp]
+        L.bcq_dequant_shape_for.restype = i32
         L.bcq_pack.argtypes = [vp, vp, i32, i64, i64, vp]
         L.bcq_unpack.argtypes = [vp, vp, i32, i64, i64, vp]
         L.bcq_gemv.argtypes = [vp, vp, i32, vp, vp, i64, i64, i32, i32, vp]
@@ -96,6 +98,14 @@ def select_kernel(variant) -> None:
 def select_dequant_shape(request_tiles: int = 0, row_blocks: int = 0) -> None:
     """Benchmarks and tests: force the workgroup shape of the large-batch kernel ((0, 0) = automatic)."""
     _check(lib().bcq_select_dequant_shape(int(request_tiles), int(row_blocks)), "bcq_select_dequant_shape")
+
+
+def dequant_shape_for(p: int, m: int, n: int, batch: int, group: int = 128, with_offsets: bool = False) -> tuple:
+    """Benchmarks and tests: the shape, as ``select_dequant_shape`` takes it, that the large-batch kernel runs such a product with."""
+    pair = (ctypes.c_int * 2)()
+    _check(lib().bcq_dequant_shape_for(p, m, n, batch, group, int(with_offsets), ctypes.byref(pair, 0), ctypes.byref(pair, 4)),
+           "bcq_dequant_shape_for")
+    return pair[0], pair[1]
 
 
 def last_kernel() -> str:

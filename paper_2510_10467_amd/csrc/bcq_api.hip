@@ -188,6 +188,24 @@ int bcq_select_dequant_shape(int request_tiles, int row_blocks)
     return bcq::dequant_mfma_force_shape(request_tiles, row_blocks) ? BCQ_OK : BCQ_ERR_VARIANT;
 }
 
+int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks)
+{
+    if (!request_tiles || !row_blocks) return BCQ_ERR_NULL;
+    if (p < 1 || p > BCQ_MAX_PLANES || check_shape(m, n, batch, group) != BCQ_OK || batch < 1) return BCQ_ERR_VARIANT;
+    static const _Float16 set{};        // (only whether there are offsets is asked)
+    bcq::GemmArgs a{};
+    a.scales[p] = &set;
+    a.offsets[p] = with_offsets ? &set : nullptr;
+    a.uniform_p = a.p_max = p;
+    a.m = m;
+    a.n = n;
+    a.batch = batch;
+    a.group = group;
+    if (!bcq::dequant_mfma_supports(a)) return BCQ_ERR_VARIANT;
+    bcq::dequant_mfma_shape(a, *request_tiles, *row_blocks);
+    return BCQ_OK;
+}
+
 int bcq_pack(const int8_t *codes, uint32_t *planes, int n_planes, int64_t m, int64_t n, void *stream)
 {
     if (!codes || !planes) return BCQ_ERR_NULL;

@@ -1299,7 +1299,7 @@ constexpr WgShape kShapes[] = {{1, 4, 0.51f, 0.32f, 0.78f, 0.39f}, {1, 2, 0.36f,
                                // (128 requests and 128 rows the same way: 28672x8192 at 128 requests 139 -> 129 us)
                                {8, 8, 2.01f, 1.48f, 0.f, 0.f}};
 
-// the cheapest shape for `batch` requests at precision p and its cost, among the shapes of at least min_nt tiles; `times`:
+// the cheapest shape for `batch` requests at precision p and its cost per group of columns, among the shapes of at least min_nt tiles; `times`:
 // that many such problems in one launch
 float cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, int times = 1)
 {
@@ -1320,6 +1320,43 @@ float cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, 
         }
     }
     return best;
+}
+
+// What a product above 32 requests is expected to take with its cheapest shape, in microseconds.  start_us: the part of a round
+// that does not depend on the width.
+float summing_us(const GemmArgs &a)
+{
+    constexpr float start_us = 3.65f;
+    int nt, rw;
+    float all = 32.f * cheapest_shape(a.uniform_p, a.m, a.batch, 1, nt, rw);
+    const int rows = 16 * row_blocks_of(nt, rw);
+    const float full = (float)((a.m + rows - 1) / rows) * (float)((a.batch + 16 * nt - 1) / (16 * nt)) / 256.f;
+    float rounds = __builtin_ceilf(full);
+    if (nt == 8 && rw == 8 && full > 1.f && a.n <= 4096) {
+        // 64 KiB of LDS: two workgroups on a CU, a second one at half to three quarters of the first (16655 x 1024 with 276 requests, 393
+        // workgroups: 31.3 us where two rounds would take 37.6); on longer rows as for the tiles of 128 x 64 of the level form
+        const float pairs = __builtin_floorf(full / 2.f), rest = full - 2.f * pairs;
+        const float price = 1.75f * pairs + (rest == 0.f ? 0.f : rest <= 1.f ? 1.f : 1.5f + 0.25f * (rest - 1.f));
+        all *= price / rounds;
+        rounds = price;
+    }
+    return large_batch_us(all, rounds * start_us, a.n);
+}
+
+// The form and shape of a product at one precision: the level form (its shape number), or -1 and the summing form.
+int level_shape_of(const GemmArgs &a)
+{
+    const int forced = level_mfma_forced_shape();
+    if (forced >= 0) return forced;
+    // Above 32 requests (up to there its tiles stand partly empty) the level form wherever it is expected to be ahead.  Of 1200 products
+    // drawn from n = 256 .. 28672, m = 1024 .. 28672 and 33 to 1000 requests it takes 668, 1.25 times as fast as the summing form on
+    // average; 6 of them are more than 3 % slower, the worst 7262 x 18432 with 149 requests at p = 4, 138 -> 154 us.
+    // 28672 x 8192 at 2048 requests and p = 3: 1271 -> 963 us; 8192 x 8192 at 96 and p = 4: 51 -> 40; 4096 x 256 at 500 and
+    // p = 4, where the start of a round decides, stays (6.9 against 8.6).
+    if (g_forced_nt != 0 || a.batch <= 32 || !level_mfma_supports(a)) return -1;
+    float us = 0.f;
+    const int shape = level_mfma_cheapest(a, us);
+    return us < summing_us(a) ? shape : -1;
 }
 
 // A batch with per-request precision beyond 64 requests: the uniform kernel's body on the requests of each
@@ -1401,6 +1438,20 @@ bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
     return true;
 }
 
+void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)
+{
+    const int level = level_shape_of(a);
+    if (level >= 0) {
+        request_tiles = 1;
+        row_blocks = 100 + level;
+        return;
+    }
+    int nt = g_forced_nt, rw = g_forced_rw;
+    if (nt == 0) cheapest_shape(a.uniform_p, a.m, a.batch, 1, nt, rw);
+    request_tiles = nt == 1 ? 0 : nt == 2 ? 32 : nt / 4;
+    row_blocks = rw;
+}
+
 bool dequant_mfma_supports(const GemmArgs &a)
 {
     // 32-bit byte offsets inside one plane / one scale plane / the activation matrix
@@ -1438,17 +1489,8 @@ hipError_t dequant_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_
 hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool planewise, const GemmArgs *mats, int count)
 {
     if (!planewise && a.uniform_p > 0) {
-        // More than 32 requests: the level form wherever its cheapest shape costs less than this one's (28672 x 8192 at 2048
-        // requests and p = 3: 1271 -> 963 us; 8192 x 8192 at 96 and p = 4: 51 -> 40); up to 32 its tiles stand partly empty.
-        const int forced = level_mfma_forced_shape();
-        if (forced >= 0) return level_mfma_supports(a) ? level_mfma_launch(a, forced, stream, mats, count) : hipErrorInvalidValue;
-        if (g_forced_nt == 0 && a.batch > 32 && level_mfma_supports(a)) {
-            int nt, rw;
-            float level_cost;
-            const float cost = cheapest_shape(a.uniform_p, a.m, a.batch, 1, nt, rw);
-            const int shape = level_mfma_cheapest(a.uniform_p, a.m, a.batch, 1, level_cost);
-            if (level_cost < cost) return level_mfma_launch(a, shape, stream, mats, count);
-        }
+        const int shape = level_shape_of(a);
+        if (shape >= 0) return level_mfma_supports(a) ? level_mfma_launch(a, shape, stream, mats, count) : hipErrorInvalidValue;
     }
     DequantParams pr{};
     pr.planes = reinterpret_cast<const unsigned char *>(a.planes);

@@ -61,6 +61,8 @@ hipError_t plane_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t 
 bool dequant_mfma_supports(const GemmArgs &a);
 // benchmarks and tests: force the workgroup shape (request tiles of 64, or 0 for one tile of 16; blocks of 16 rows); (0, 0) = automatic
 bool dequant_mfma_force_shape(int request_tiles, int row_blocks);
+// the shape that a product at one precision runs with, forced or automatic, as the pair bcq_select_dequant_shape takes
+void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks);
 // planewise: the variant that multiplies the +-1 planes themselves and scales the group sums (groups of 128 or 256)
 hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool planewise = false, const GemmArgs *mats = nullptr, int count = 0);
 // several matrices (same n, precision, batch, activations, group size; no offsets) in one launch of the large-batch kernels
@@ -69,8 +71,14 @@ hipError_t dequant_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_
 
 // The level form of the large-batch kernels: weights rebuilt by look-ups, tiles of 32 x 32 (dequant_mfma_launch picks it).
 bool level_mfma_supports(const GemmArgs &a);
-// its cheapest shape for `times` problems of m rows and `batch` requests in one launch, and the cost per 128 columns
-int level_mfma_cheapest(int p, int64_t m, int batch, int times, float &cost);
+// its cheapest shape for a product, and what that one is expected to take in microseconds
+int level_mfma_cheapest(const GemmArgs &a, float &us);
+// The estimate of both large-batch forms: `at_4096` is what a product of 4096 columns takes, of which `start` does not depend
+// on the width (beyond 4096 columns it no longer counts).
+inline float large_batch_us(float at_4096, float start, int64_t n)
+{
+    return n < 4096 ? start + (at_4096 - start) * ((float)n / 4096.f) : at_4096 * ((float)n / 4096.f);
+}
 bool level_mfma_force_shape(int shape);         // benchmarks and tests; -1: automatic
 int level_mfma_forced_shape();
 hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count);

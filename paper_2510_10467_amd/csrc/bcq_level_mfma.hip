@@ -456,19 +456,22 @@ hipError_t launch_shape(const LevelParams &pr, int p, bool offset, hipStream_t s
     }
 }
 
-// Shapes and what a grid of each costs: microseconds per 128 columns with 256 and with 128 workgroups on the chip (n = 4096),
-// p = 4 and p = 2.  Their LDS allows one workgroup per CU, so a call costs its rounds of workgroups over the 256 CUs; a
-// round that fills half of the chip is quicker by up to a third, because with random operands the full one is held back by
-// power (256 x 256, p = 2, per pair of groups: 7.6 us on 256 CUs, 5.6 on 128, and 5.3 on 256 with activations of zero).
-// The costs are compared with those of the other form (cheapest_shape).  Large tiles rebuild a weight for more requests, small
-// ones keep the CUs busy on short matrices and batches.
+// Shapes and what a grid of each costs: microseconds per 128 columns with 256 and with at most 128 workgroups on the chip (n = 4096),
+// p = 4 and p = 2.  A call costs its rounds of workgroups over the 256 CUs; a round that fills half of the chip is quicker by up to
+// a third, because with random operands the full one is held back by power (256 x 256, p = 2, per pair of groups: 7.6 us on 256
+// CUs, 5.6 on 128, and 5.3 on 256 with activations of zero).  start_us is the part of a round that does not shrink with the width: the
+// first three stages of activations have to arrive, the results to leave, the launch itself (4096 x 256 with 500 requests at
+// p = 4 on 128 x 128: 8.5 us, where an eighth of the columns' share of 4096 x 4096 would be 3).
+// The LDS of the tiles of 128 x 64 (64 KiB, and at most 116 registers) lets two of those workgroups share a CU, that of the others
+// one.  Large tiles rebuild a weight for more requests, small ones keep the CUs busy on short matrices and batches.
 struct LevelShape {
     int rows, reqs;
-    float full_p4, full_p2, half_p4, half_p2;
+    float full_p4, full_p2, half_p4, half_p2, start_us;
 };
-constexpr LevelShape kLevelShapes[] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f},
-                                       {128, 128, 1.62f, 1.34f, 1.43f, 1.06f}, {64, 128, 1.07f, 0.97f, 0.92f, 0.81f},
-                                       {128, 64, 1.11f, 0.82f, 1.00f, 0.72f},  {64, 64, 0.69f, 0.56f, 0.67f, 0.47f}};
+constexpr LevelShape kLevelShapes[] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f, 7.65f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f, 5.25f},
+                                       {128, 128, 1.62f, 1.34f, 1.43f, 1.06f, 5.65f}, {64, 128, 1.07f, 0.97f, 0.92f, 0.81f, 6.15f},
+                                       {128, 64, 1.11f, 0.82f, 1.00f, 0.72f, 3.65f},  {64, 64, 0.69f, 0.56f, 0.67f, 0.47f, 4.65f}};
+constexpr int kTwoPerCu = 4;        // 128 x 64
 constexpr int kLevelShapeCount = 6;
 thread_local int g_forced_shape = -1;
 
@@ -486,20 +489,30 @@ int level_mfma_forced_shape() { return g_forced_shape; }
 // whole pairs of 128-column groups; 32-bit byte offsets are the caller's condition (dequant_mfma_supports)
 bool level_mfma_supports(const GemmArgs &a) { return a.uniform_p >= 1 && a.uniform_p <= kMaxP && a.n % 256 == 0; }
 
-int level_mfma_cheapest(int p, int64_t m, int batch, int times, float &cost)
+int level_mfma_cheapest(const GemmArgs &a, float &us)
 {
+    const int p = a.uniform_p;
     int best = -1;
     for (int k = 0; k < kLevelShapeCount; ++k) {
         const LevelShape &c = kLevelShapes[k];
-        const float wgs = (float)((m + c.rows - 1) / c.rows) * (float)((batch + c.reqs - 1) / c.reqs) * (float)times;
+        const float wgs = (float)((a.m + c.rows - 1) / c.rows) * (float)((a.batch + c.reqs - 1) / c.reqs);
         const float full = p >= 3 ? c.full_p4 : c.full_p2, half = p >= 3 ? c.half_p4 : c.half_p2;
         const float rounds = __builtin_floorf(wgs / 256.f), rest = wgs / 256.f - rounds;
-        const float all = rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f));
-        if (best < 0 || all < cost) {
+        float all = 32.f * (rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f)));
+        // Two workgroups on a CU (4096 columns, p = 4: 256 of them take 36.9 us, 320 59.0, 512 64.0) on longer rows lose it again:
+        // a lane reads 16 bytes of a row at a time, and the lines of that many rows do not stay in L2 from one read to the next
+        // (21248 x 8192 with 587 requests at p = 4: 1.7 times what 4096 columns would let one expect).
+        if (k == kTwoPerCu && wgs > 256.f && a.n <= 4096) all *= 0.85f;
+        const float start = c.start_us * __builtin_ceilf(wgs / 256.f);
+        all = large_batch_us(all, start, a.n);
+        if (best < 0 || all < us) {
             best = k;
-            cost = all;
+            us = all;
         }
     }
+    // Sixteen levels (p = 4 with offsets) take two look-ups per byte: 1.08 to 1.2 times the time, where the summing form takes 1.0 to
+    // 1.02 times its own.  At p <= 2 the summing form takes about 1.05 times the time its prices say.
+    us *= p == 4 && a.offsets[p] ? 1.1f : p <= 2 ? 0.95f : 1.f;
     return best;
 }
 

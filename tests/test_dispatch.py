@@ -1,0 +1,64 @@
+"""The choice between the two forms of the large-batch kernel: host code, no GPU needed.  Pairs (1, 100) and above are the level form
+(weights by look-up), every other pair is the summing form."""
+import pytest
+
+import paper_2510_10467_amd as bcq
+from paper_2510_10467_amd import build as hip_build
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if hip_build.is_stale():
+        hip_build.build()
+
+
+def takes_level_form(p, m, n, batch, group=128, with_offsets=False):
+    tiles, blocks = bcq.dequant_shape_for(p, m, n, batch, group, with_offsets)
+    return tiles == 1 and blocks >= 100
+
+
+# (p, m, n, batch, group, offsets): microseconds on one MI355X of the summing form and of the level form's best shape for that call
+SUMMING_IS_AHEAD = [
+    ((4, 13824, 256, 90, 256, True), 5.8, 6.3),         # what a round takes at any width decides on narrow matrices
+    ((2, 6144, 256, 105, 128, False), 4.3, 5.1),
+    ((4, 4864, 256, 153, 64, False), 5.1, 5.8),
+    ((2, 2816, 512, 229, 64, True), 5.5, 6.2),
+    ((4, 11542, 1024, 46, 64, True), 9.4, 10.9),
+    ((4, 1024, 1280, 320, 128, False), 7.3, 9.1),       # widths that leave the teams of a workgroup unequal shares
+    ((4, 4096, 1280, 128, 128, False), 8.0, 9.7),
+    ((4, 16655, 1024, 276, 128, True), 31.3, 35.0),     # sixteen levels
+    ((4, 5289, 11520, 955, 128, True), 246.9, 254.4),
+    ((4, 13824, 18688, 497, 256, True), 424.8, 478.0),
+]
+
+LEVEL_IS_AHEAD = [
+    ((3, 28672, 8192, 2048, 128, False), 1271.0, 963.0),
+    ((4, 8192, 8192, 96, 64, False), 51.0, 40.0),
+    ((3, 8935, 8960, 211, 128, False), 103.0, 75.4),
+    ((4, 5632, 26624, 189, 64, False), 195.7, 157.6),
+    ((4, 3208, 16384, 365, 128, False), 127.5, 100.9),
+    ((2, 9397, 3584, 184, 128, True), 32.2, 22.4),
+    ((1, 17408, 27904, 161, 128, True), 343.9, 231.0),
+]
+
+
+@pytest.mark.parametrize("call,summing_us,level_us", SUMMING_IS_AHEAD)
+def test_summing_form_where_it_is_ahead(call, summing_us, level_us):
+    assert not takes_level_form(*call)
+
+
+@pytest.mark.parametrize("call,summing_us,level_us", LEVEL_IS_AHEAD)
+def test_level_form_where_it_is_ahead(call, summing_us, level_us):
+    assert takes_level_form(*call)
+
+
+def test_what_the_level_form_does_not_take():
+    assert takes_level_form(4, 28672, 8192, 33)
+    assert not takes_level_form(4, 28672, 8192, 32)             # one tile of 32 requests
+    assert takes_level_form(4, 28672, 8192, 500)
+    assert not takes_level_form(4, 28672, 8192 + 128, 500)      # not whole pairs of column groups
+    for bad in ((5, 28672, 8192, 500, 128), (4, 28672, 8192, 500, 32), (0, 28672, 8192, 500, 128), (4, 0, 8192, 500, 128), (4, 28672, 8192, 0, 128)):
+        with pytest.raises(bcq.BcqError) as error:              # five planes, groups of 32, no problem at all
+            bcq.dequant_shape_for(*bad)
+        assert error.value.status == -6
+    assert bcq.lib().bcq_dequant_shape_for(4, 28672, 8192, 500, 128, 0, None, None) == -1
