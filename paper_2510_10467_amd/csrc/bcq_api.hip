@@ -119,7 +119,7 @@ int run(const bcq::GemmArgs &a, hipStream_t stream)
         g_last = plane_mfma_streams(a) ? "plane_mfma_rows" : "plane_mfma";      // (the row-streaming form of the family)
         break;
     case BCQ_KERNEL_DEQUANT_MFMA:
-        if (!dequant_mfma_supports(a)) return BCQ_ERR_VARIANT;
+        if (!dequant_mfma_supports(a) || !dequant_mfma_shape_fits(a)) return BCQ_ERR_VARIANT;
         err = dequant_mfma_launch(a, stream);
         g_last = "dequant_mfma";
         break;
@@ -201,7 +201,7 @@ int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int
     a.n = n;
     a.batch = batch;
     a.group = group;
-    if (!bcq::dequant_mfma_supports(a)) return BCQ_ERR_VARIANT;
+    if (!bcq::dequant_mfma_supports(a) || !bcq::dequant_mfma_shape_fits(a)) return BCQ_ERR_VARIANT;
     bcq::dequant_mfma_shape(a, *request_tiles, *row_blocks);
     return BCQ_OK;
 }
@@ -339,6 +339,7 @@ int bcq_gemv_multi(int count, const uint32_t *const *planes, const bcq_half *con
         all.m = 0;
         for (int k = 0; k < count; ++k) all.m += mats[k].m;
         const int c = choose(all);
+        if (c == BCQ_KERNEL_DEQUANT_MFMA && !bcq::dequant_mfma_shape_fits(all)) return BCQ_ERR_VARIANT;
         if ((c == BCQ_KERNEL_PLANE_F16 && group >= 128) || c == BCQ_KERNEL_DEQUANT_MFMA) {
             g_last = c == BCQ_KERNEL_PLANE_F16 ? "plane_f16" : "dequant_mfma";
             return bcq::dequant_mfma_launch_multi(mats, count, static_cast<hipStream_t>(stream), c == BCQ_KERNEL_PLANE_F16) == hipSuccess

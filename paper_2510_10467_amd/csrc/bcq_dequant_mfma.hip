@@ -1438,6 +1438,11 @@ bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
     return true;
 }
 
+bool dequant_mfma_shape_fits(const GemmArgs &a)
+{
+    return a.uniform_p == 0 || level_mfma_forced_shape() < 0 || level_mfma_supports(a);
+}
+
 void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)
 {
     const int level = level_shape_of(a);
@@ -1490,7 +1495,7 @@ hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool plane
 {
     if (!planewise && a.uniform_p > 0) {
         const int shape = level_shape_of(a);
-        if (shape >= 0) return level_mfma_supports(a) ? level_mfma_launch(a, shape, stream, mats, count) : hipErrorInvalidValue;
+        if (shape >= 0) return level_mfma_launch(a, shape, stream, mats, count);
     }
     DequantParams pr{};
     pr.planes = reinterpret_cast<const unsigned char *>(a.planes);

@@ -61,6 +61,8 @@ hipError_t plane_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t 
 bool dequant_mfma_supports(const GemmArgs &a);
 // benchmarks and tests: force the workgroup shape (request tiles of 64, or 0 for one tile of 16; blocks of 16 rows); (0, 0) = automatic
 bool dequant_mfma_force_shape(int request_tiles, int row_blocks);
+// whether the forced shape, if there is one, can run the problem (the level form takes whole pairs of column groups only)
+bool dequant_mfma_shape_fits(const GemmArgs &a);
 // the shape that a product at one precision runs with, forced or automatic, as the pair bcq_select_dequant_shape takes
 void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks);
 // planewise: the variant that multiplies the +-1 planes themselves and scales the group sums (groups of 128 or 256)

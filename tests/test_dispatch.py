@@ -1,5 +1,7 @@
 """The choice between the two forms of the large-batch kernel: host code, no GPU needed.  Pairs (1, 100) and above are the level form
 (weights by look-up), every other pair is the summing form."""
+import ctypes
+
 import pytest
 
 import paper_2510_10467_amd as bcq
@@ -62,3 +64,28 @@ def test_what_the_level_form_does_not_take():
             bcq.dequant_shape_for(*bad)
         assert error.value.status == -6
     assert bcq.lib().bcq_dequant_shape_for(4, 28672, 8192, 500, 128, 0, None, None) == -1
+
+
+@pytest.fixture
+def knobs():
+    yield
+    bcq.select_dequant_shape(0, 0)
+    bcq.select_kernel("auto")
+
+
+def test_forced_level_form_refuses_what_it_does_not_take(knobs):
+    """A forced shape that cannot run the problem is reported as that (-6) before anything is launched (made-up addresses do), from
+    every entry point; per-request precision never runs on the level form and is not concerned."""
+    L = bcq.lib()
+    P, S, X, Y = 0x10000, 0x20000, 0x30000, 0x40000
+    bcq.select_kernel("dequant_mfma")
+    bcq.select_dequant_shape(1, 102)
+    assert L.bcq_gemv(P, S, 3, X, Y, 4096, 640, 70, 128, None) == -6
+    assert L.bcq_gemv_offset(P, S, S, 3, X, Y, 4096, 640, 70, 128, None) == -6
+    assert L.bcq_dequant_shape_for(3, 4096, 640, 70, 128, 0, ctypes.byref(ctypes.c_int()), ctypes.byref(ctypes.c_int())) == -6
+    pp = (ctypes.c_void_p * 2)(P, P + 0x1000)
+    sp = (ctypes.c_void_p * 2)(S, S + 0x1000)
+    yp = (ctypes.c_void_p * 2)(Y, Y + 0x1000)
+    assert L.bcq_gemv_multi(2, pp, sp, (ctypes.c_int64 * 2)(4096, 4096), yp, 3, X, 640, 70, 128, None) == -6
+    bcq.select_kernel("auto")
+    assert L.bcq_gemv(P, S, 3, X, Y, 14336, 640, 70, 128, None) == -6
