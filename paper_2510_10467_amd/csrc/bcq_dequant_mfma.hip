@@ -63,7 +63,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxP = 4;
 constexpr int kClassFrom = 64;              // per-request precision: beyond this many requests the uniform kernel's body per precision
-thread_local int g_forced_nt = 0, g_forced_rw = 0;       // workgroup shape forced by dequant_mfma_force_shape (0: automatic)
+// workgroup shape forced by dequant_mfma_force_shape: of this file's kernels (0: automatic) or of the level form (-1: none), never both
+thread_local int g_forced_nt = 0, g_forced_rw = 0, g_forced_level = -1;
 constexpr int kLutBytes = 256;              // 16 entries x 8 bytes, rounded up to keep what follows aligned
 constexpr int kXRowBytes = 128 * 2;         // LDS row of one request's 128 activations; its sixteen parts sit XOR-permuted
 
@@ -1346,8 +1347,7 @@ float summing_us(const GemmArgs &a)
 // The form and shape of a product at one precision: the level form (its shape number), or -1 and the summing form.
 int level_shape_of(const GemmArgs &a)
 {
-    const int forced = level_mfma_forced_shape();
-    if (forced >= 0) return forced;
+    if (g_forced_level >= 0) return g_forced_level;
     // Above 32 requests (up to there its tiles stand partly empty) the level form wherever it is expected to be ahead.  Of 1200 products
     // drawn from n = 256 .. 28672, m = 1024 .. 28672 and 33 to 1000 requests it takes 668, 1.25 times as fast as the summing form on
     // average; 6 of them are more than 3 % slower, the worst 7262 x 18432 with 149 requests at p = 4, 138 -> 154 us.
@@ -1422,10 +1422,9 @@ hipError_t launch_p(const DequantParams &pr, const GemmArgs &a, hipStream_t stre
 // request_tiles: 1, 2 or 4 tiles of 64 requests, or 0 (with row_blocks != 0) for a single tile of 16 requests
 bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
 {
-    if (request_tiles == 1 && row_blocks >= 100) return level_mfma_force_shape(row_blocks - 100);
-    level_mfma_force_shape(-1);
-    if (request_tiles == 0 && row_blocks == 0) {
+    if ((request_tiles == 0 && row_blocks == 0) || (request_tiles == 1 && row_blocks >= 100 && row_blocks < 100 + kLevelShapeCount)) {
         g_forced_nt = g_forced_rw = 0;
+        g_forced_level = request_tiles == 0 ? -1 : row_blocks - 100;
         return true;
     }
     const int nt = request_tiles == 0 ? 1 : request_tiles == 32 ? 2 : 4 * request_tiles;      // 32: a tile of 32 requests
@@ -1435,12 +1434,13 @@ bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
     if (!known || request_tiles < 0 || (row_blocks != 1 && row_blocks != 2 && row_blocks != 4 && row_blocks != 8 && row_blocks != 40)) return false;
     g_forced_nt = nt;
     g_forced_rw = row_blocks;
+    g_forced_level = -1;
     return true;
 }
 
 bool dequant_mfma_shape_fits(const GemmArgs &a)
 {
-    return a.uniform_p == 0 || level_mfma_forced_shape() < 0 || level_mfma_supports(a);
+    return a.uniform_p == 0 || g_forced_level < 0 || level_mfma_supports(a);
 }
 
 void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)

@@ -72,6 +72,7 @@ bool dequant_mfma_supports_multi(const GemmArgs *mats, int count);
 hipError_t dequant_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t stream, bool planewise);
 
 // The level form of the large-batch kernels: weights rebuilt by look-ups, tiles of 32 x 32 (dequant_mfma_launch picks it).
+constexpr int kLevelShapeCount = 6;
 bool level_mfma_supports(const GemmArgs &a);
 // its cheapest shape for a product, and what that one is expected to take in microseconds
 int level_mfma_cheapest(const GemmArgs &a, float &us);
@@ -81,8 +82,6 @@ inline float large_batch_us(float at_4096, float start, int64_t n)
 {
     return n < 4096 ? start + (at_4096 - start) * ((float)n / 4096.f) : at_4096 * ((float)n / 4096.f);
 }
-bool level_mfma_force_shape(int shape);         // benchmarks and tests; -1: automatic
-int level_mfma_forced_shape();
 hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count);
 
 // Offline quantiser (Algorithm 1): group must be 32, 64, 128 or 256; 1 <= p_low <= p_high <= 4.

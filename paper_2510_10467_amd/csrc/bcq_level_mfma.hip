@@ -468,23 +468,12 @@ struct LevelShape {
     int rows, reqs;
     float full_p4, full_p2, half_p4, half_p2, start_us;
 };
-constexpr LevelShape kLevelShapes[] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f, 7.65f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f, 5.25f},
+constexpr LevelShape kLevelShapes[kLevelShapeCount] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f, 7.65f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f, 5.25f},
                                        {128, 128, 1.62f, 1.34f, 1.43f, 1.06f, 5.65f}, {64, 128, 1.07f, 0.97f, 0.92f, 0.81f, 6.15f},
                                        {128, 64, 1.11f, 0.82f, 1.00f, 0.72f, 3.65f},  {64, 64, 0.69f, 0.56f, 0.67f, 0.47f, 4.65f}};
 constexpr int kTwoPerCu = 4;        // 128 x 64
-constexpr int kLevelShapeCount = 6;
-thread_local int g_forced_shape = -1;
 
 }  // namespace
-
-bool level_mfma_force_shape(int shape)
-{
-    if (shape >= kLevelShapeCount) return false;
-    g_forced_shape = shape;
-    return true;
-}
-
-int level_mfma_forced_shape() { return g_forced_shape; }
 
 // whole pairs of 128-column groups; 32-bit byte offsets are the caller's condition (dequant_mfma_supports)
 bool level_mfma_supports(const GemmArgs &a) { return a.uniform_p >= 1 && a.uniform_p <= kMaxP && a.n % 256 == 0; }

@@ -89,3 +89,14 @@ def test_forced_level_form_refuses_what_it_does_not_take(knobs):
     assert L.bcq_gemv_multi(2, pp, sp, (ctypes.c_int64 * 2)(4096, 4096), yp, 3, X, 640, 70, 128, None) == -6
     bcq.select_kernel("auto")
     assert L.bcq_gemv(P, S, 3, X, Y, 14336, 640, 70, 128, None) == -6
+
+
+def test_a_refused_shape_changes_nothing(knobs):
+    for forced in ((1, 103), (4, 8), (32, 2)):
+        bcq.select_dequant_shape(*forced)
+        for refused in ((3, 4), (1, 106), (1, 99), (-1, 4), (7, 7), (2, 100)):
+            with pytest.raises(bcq.BcqError):
+                bcq.select_dequant_shape(*refused)
+            assert bcq.dequant_shape_for(4, 28672, 8192, 500) == forced
+    bcq.select_dequant_shape(0, 0)
+    assert bcq.dequant_shape_for(4, 28672, 8192, 500) not in ((1, 103), (4, 8), (32, 2))
