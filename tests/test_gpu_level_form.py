@@ -1,0 +1,122 @@
+"""The two forms of the large-batch kernel against each other and bit for bit against the definition: the level form (weights by
+look-up, codes 100 .. 105 of the forced shapes) and the summing form, on shapes that the automatic choice would give to either."""
+import numpy as np
+import pytest
+
+import synthetic_inputs as syn
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 100), (1, 101), (1, 102), (1, 103), (1, 104), (1, 105), (1, 4), (4, 8)]       # the last two: the summing form
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from tests import gpu_util
+    return gpu_util
+
+
+@pytest.fixture
+def force():
+    import paper_2510_10467_amd as bcq
+
+    def forced(shape):
+        print(f"shape {shape}", flush=True)
+        bcq.select_kernel("dequant_mfma")
+        bcq.select_dequant_shape(*shape)
+    yield forced
+    bcq.select_dequant_shape(0, 0)
+    bcq.select_kernel("auto")
+
+
+def weights16(layer, p, group, offsets):
+    """W_p: z + (+-alpha_1) + ... in float32, plane by plane, rounded once to binary16."""
+    bits = np.unpackbits(layer.planes.view(np.uint8), axis=-1, bitorder="little").astype(bool)
+    w = np.zeros((layer.m, layer.n), dtype=np.float32)
+    if offsets is not None:
+        w += np.repeat(offsets.astype(np.float32), group, axis=1)
+    for i in range(p):
+        a = np.repeat(layer.scales[p][i].astype(np.float32), group, axis=1)
+        w = w + np.where(bits[i], a, -a)
+    return w.astype(np.float16)
+
+
+@pytest.mark.parametrize("n,group", [(512, 64), (512, 128), (768, 256)])
+@pytest.mark.parametrize("with_offsets", [False, True])
+def test_every_weight_bit_for_bit(gpu, force, n, group, with_offsets):
+    """One-hot activations read every weight of two and three pairs of column groups: a wrong byte of a look-up, a swapped column or a
+    second rounding shows, where the tolerance of a whole product would hide it.  300 rows: a ragged last tile in every shape."""
+    import paper_2510_10467_amd as bcq
+    m = 300
+    layer = syn.make_layer(m, n, group=group, seed=(950, n, group), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = gpu.to_dev(np.eye(n, dtype=np.float16))
+    for p in (1, 2, 3, 4):
+        z = syn.make_offsets(p, m, n, group, seed=(951, n, p)) if with_offsets else None
+        expected = weights16(layer, p, group, z).T.view(np.uint16)
+        for shape in SHAPES:
+            force(shape)
+            y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x, group=group, offsets=None if z is None else gpu.to_dev(z))
+            got = (y + 0.0).cpu().numpy().view(np.uint16)           # (-0 and +0 are the same weight)
+            wrong = np.argwhere(got != (expected.view(np.float16) + np.float16(0)).view(np.uint16))
+            assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+def test_products_that_are_exact(gpu, force, shape):
+    """Scales of 1, 1/4, 1/16, 1/64 and whole activations up to 8: every partial sum is a multiple of 1/64 below 2^14 and therefore
+    exact in float32, so each result is the exact one rounded once to binary16, whatever the order.  Planes from p on are
+    not read, and the same call gives the same bits on ordinary inputs too."""
+    import torch
+
+    import paper_2510_10467_amd as bcq
+    m, n, batch = 290, 1280, 70
+    layer = syn.make_layer(m, n, seed=(952, 0), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    whole = np.random.default_rng([syn.BASE_SEED, 952]).integers(-8, 9, size=(batch, n)).astype(np.float16)
+    x = gpu.to_dev(syn.make_x(batch, n, seed=(952, 1)))
+    force(shape)
+    for p in (1, 2, 3, 4):
+        powers = np.repeat(np.array([1, 0.25, 0.0625, 0.015625], dtype=np.float16)[:p], m * n // 128).reshape(p, m, n // 128)
+        exact = whole.astype(np.float64) @ weights16(syn.BcqLayer(m, n, 128, layer.planes, {p: powers}), p, 128, None).astype(np.float64).T
+        y = bcq.bcq_gemv(dl.planes, gpu.to_dev(powers), p, gpu.to_dev(whole)).cpu().numpy()
+        assert np.array_equal(y, exact.astype(np.float16)), f"shape {shape} p={p}"
+        other = dl.planes.clone()
+        other[p:] = ~other[p:]
+        y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x)
+        assert torch.equal(y, bcq.bcq_gemv(dl.planes, dl.scales[p], p, x)), f"shape {shape} p={p}: not deterministic"
+        assert torch.equal(y, bcq.bcq_gemv(other, dl.scales[p], p, x)), f"shape {shape} p={p}: planes >= p influenced the result"
+
+
+@pytest.mark.parametrize("group", [64, 256])
+@pytest.mark.parametrize("shape", [(1, 2), (2, 4), (4, 40), (2, 8)])
+def test_summing_form_where_the_level_form_is_the_default(gpu, force, group, shape):
+    """Groups of 64 and 256 with and without offsets, of which the automatic choice leaves the summing form little above 32 requests."""
+    m, n, batch = 150, 1536, 70
+    layer = syn.make_layer(m, n, group=group, seed=(953, group), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = syn.make_x(batch, n, seed=(953, 1))
+    force(shape)
+    for p in (1, 2, 3, 4):
+        for z in (None, syn.make_offsets(p, m, n, group, seed=(954, p))):
+            gpu.check_gemv(dl, p, x, "dequant_mfma", group, offsets=z)
+
+
+def test_both_forms_at_the_limit_of_32_bit_offsets(gpu, oracle, force):
+    """Two planes of just under 2 GiB, past 2^31 bytes in 32-bit offsets: sampled rows of either form against the oracle."""
+    import paper_2510_10467_amd as bcq
+    m, n, p, batch = 262144 - 11, 65536, 2, 80
+    layer = syn.make_layer(m, n, p_max=p, seed=(280, m, p), precisions=[p], signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = syn.make_x(batch, n, seed=(280, batch))
+    rows = np.unique(np.concatenate([[0, 31, 32, 131071, 131072, m - 65, m - 33, m - 32, m - 1],
+                                     np.random.default_rng([syn.BASE_SEED, 955]).integers(0, m, size=40)]))
+    y_ref, a_ref = oracle.gemv(np.ascontiguousarray(layer.planes[:, rows, :]), np.ascontiguousarray(layer.scales[p][:, rows, :]), x)
+    for shape in ((1, 105), (1, 101), (1, 4)):
+        force(shape)
+        out = gpu.Guarded((batch, m))
+        bcq.bcq_gemv(dl.planes, dl.scales[p], p, gpu.to_dev(x), y=out.t)
+        y = out.check(f"shape {shape}")
+        gpu.assert_within_tolerance(y[:, rows], y_ref, a_ref, f"shape {shape}")
