@@ -127,12 +127,14 @@ def run_suite(args, torch, bcq, syn, dev):
     rows = []
     launches = 16
 
-    def bench_shape(m, n, batches, precisions, mixed=False, offsets=False):
+    def bench_shape(m, n, batches, precisions, mixed=False, offsets=False, zero_x=False):
         copies = max(2, -(-MIN_ROTATION_BYTES // (m * n // 2)))
         copies = min(copies, 24)
         sets = [device_layer(m, n) for _ in range(copies)]
         for batch in batches:
             x = torch.randn((batch, n), device=dev, generator=gen).half()
+            if zero_x:
+                x.zero_()
             y = torch.empty((batch, m), dtype=torch.float16, device=dev)
             for p in precisions:
                 # asymmetric scheme: one fp16 offset per (row, group), N(0, 0.01^2), one set per precision
@@ -145,7 +147,7 @@ def run_suite(args, torch, bcq, syn, dev):
                 us = timed_graph(burst) * 1e3 / launches
                 by = syn.algorithmic_bytes(m, n, p, batch) + (m * (n // syn.GROUP) * 2 if offsets else 0)
                 rows.append({"m": m, "n": n, "batch": batch, "p": p, "offsets": bool(offsets), "kernel": bcq.last_kernel(), "us": round(us, 2),
-                             "GBps": round(by / us / 1e3, 1), "pct_of_hbm_peak": round(100 * by / us / 1e3 / HBM_PEAK_GBS, 2),
+                             "activations": "zero" if zero_x else "random", "GBps": round(by / us / 1e3, 1), "pct_of_hbm_peak": round(100 * by / us / 1e3 / HBM_PEAK_GBS, 2),
                              "TFLOPs": round(2.0 * m * n * batch / us / 1e6, 1)})
             if mixed:
                 p_req_h = syn.make_p_req(batch, 2, 4, seed=(4, batch))
@@ -283,9 +285,9 @@ def run_suite(args, torch, bcq, syn, dev):
         # Bound by double-precision vector arithmetic: per weight and cycle the base stage adds p signed terms
         # and compares against 2^p levels (sub + compare), an expansion stage to p bits spends p + 1 operations
         # (p - 1 level terms, the residual, the signed sum); the per-group solves add about one more per cycle.
+        # A wave leaves a stage once none of its groups changes a code, so how many of the cycles run depends on the weights:
+        # the rows give time and weights per second, and no operation rate.
         p_low, p_high, cycles = 2, 4, 20
-        ops_per_weight = cycles * ((p_low + 2 * 2 ** p_low + 1) + sum(p + 2 for p in range(p_low + 1, p_high + 1))) + 3 * p_low
-        peak_ops = 256 * 4 * 16 * 2.4e9                               # lanes x clock: one double operation per lane and cycle
         import time
 
         import numpy as np
@@ -306,21 +308,19 @@ def run_suite(args, torch, bcq, syn, dev):
                 torch.cuda.synchronize()
                 ms = e0.elapsed_time(e1) / reps
                 rows.append({"shape": f"{m}x{n}", "p_low": p_low, "p_high": p_high, "cycles": cycles, "offset": with_offset,
-                             "ms": round(ms, 3), "Gweights_per_s": round(m * n / ms / 1e6, 2),
-                             "roofline": {"bound": "alu", "unit": "Tops/s (fp64 lane operations)",
-                                          "achieved": round(ops_per_weight * m * n / ms / 1e9, 2),
-                                          "peak": round(peak_ops / 1e12, 2),
-                                          "frac": round(ops_per_weight * m * n / (ms * 1e-3) / peak_ops, 4)}})
+                             "ms": round(ms, 3), "Gweights_per_s": round(m * n / ms / 1e6, 2)})
         sample = syn.make_weights(512, 4096, seed=(8, 0))
         t0 = time.perf_counter()
         oracle.quantize(sample, p_low, p_high, cycles)
         dt = time.perf_counter() - t0
         rows.append({"cpu_baseline": {"value": round(sample.size / dt / 1e9, 5), "unit": "Gweights/s", "cores": oracle.num_threads(),
                                       "kind": "oracle", "sample": "512x4096 weights, p 2..4, T = 20, symmetric"}})
-        return {"suite": args.suite, "unit": "ms per matrix", "data": "synthetic", "ops_per_weight": ops_per_weight, "rows": rows}
+        return {"suite": args.suite, "unit": "ms per matrix", "data": "synthetic", "rows": rows}
     else:
         for (_, m, n) in syn.LLAMA3_70B_SHAPES:
-            bench_shape(m, n, (1, 16, 64, 256), PRECISIONS)
+            bench_shape(m, n, (1, 16, 64, 256, 2048), PRECISIONS)
+        # the same launches with activations of zero: what the time owes to the power that random operands draw
+        bench_shape(28672, 8192, (2048,), PRECISIONS, zero_x=True)
     return {"suite": args.suite, "unit": "us per call", "data": "synthetic", "rows": rows}
 
 
