@@ -1351,7 +1351,7 @@ int level_shape_of(const GemmArgs &a)
     // Above 32 requests (up to there its tiles stand partly empty) the level form wherever it is expected to be ahead.  Of 1200 products
     // drawn from n = 256 .. 28672, m = 1024 .. 28672 and 33 to 1000 requests it takes 668, 1.25 times as fast as the summing form on
     // average; 6 of them are more than 3 % slower, the worst 7262 x 18432 with 149 requests at p = 4, 138 -> 154 us.
-    // 28672 x 8192 at 2048 requests and p = 3: 1271 -> 963 us; 8192 x 8192 at 96 and p = 4: 51 -> 40; 4096 x 256 at 500 and
+    // 28672 x 8192 at 2048 requests and p = 3: 1182 -> 917 us; 8192 x 8192 at 96 and p = 4: 48 -> 38; 4096 x 256 at 500 and
     // p = 4, where the start of a round decides, stays (6.9 against 8.6).
     if (g_forced_nt != 0 || a.batch <= 32 || !level_mfma_supports(a)) return -1;
     float us = 0.f;

@@ -3,8 +3,9 @@
 // its row once per group (the same fp32 sums in the same order, rounded once to binary16, that the other form makes for
 // every weight) and keeps them in four registers, the low bytes and the high bytes of eight levels.  The p plane
 // words of 32 columns become 32 codes of p bits in two byte transposes, and a V_PERM_B32 with four codes as its selector
-// delivers one byte of four weights.  That is about 2.5 vector instructions per weight (p = 3: bit transpose 13, byte
-// transpose 8, selectors 12 and look-ups 32 per 32 columns) where the sums take about six and two LDS reads per plane.
+// delivers one byte of four weights.  At p = 3 that is 65 vector instructions per 32 columns (bit transpose 13, byte transpose 8,
+// selectors 12, look-ups 32); with the forming of the levels and the addresses the counters say 2.5 / 2.8 / 3.5 per weight
+// at p = 2 / 3 / 4, where the sums take 6.8 at p = 4, and an LDS read per weight besides the operands.
 //   p <= 3            2^p <= 8 levels, one pair of registers per byte
 //   p = 4             the levels come in pairs +-l: eight of them are kept, the codes of planes 0..2 are complemented where
 //                     plane 3 is -1 and the sign goes onto the high byte
@@ -26,11 +27,12 @@
 // A workgroup is TEAMS teams of WR x WQ waves; the teams take alternate pairs of groups with tiles of their own and meet at
 // the end (short matrices: rows alone do not fill the chip).
 //
-// What bounds it: matrix instructions and, with the chip full and random data, power: 28672 x 8192 with 2048 requests at p = 3
-// 1203 -> 923 us = 1042 TFLOP/s, where the library's plain fp16 product of 8192^3 reaches 1211 (1751 with zeros).  Smaller
-// tiles are bound by the look-ups (four matrix instructions of 32 cycles and about 30 vector instructions of 4 per step of
-// 32 rows x 128 requests).  8192 x 8192 in groups of 64 with 96 requests 47.8 -> 38.1 us; the linear layers of a Llama-3-8B
-// block with 500 requests at p = 4 422 -> 332 us.
+// What bounds it: on a full chip the matrix instructions with the look-ups between them (matrix pipe busy for 63 / 55 / 47 % of the
+// cycles at p = 2 / 3 / 4) and the clock, which random operands hold at 1.7 to 1.95 GHz (with activations of zero the same cycles
+// pass at 2.3 to 2.4): 28672 x 8192 with 2048 requests at p = 3 1182 -> 917 us = 1049 TFLOP/s, where the library's plain fp16
+// product of 8192^3 reaches 1210 (1750 with zeros).  Smaller tiles are bound by the look-ups (four matrix instructions of 32 cycles
+// and about 30 vector instructions of 4 per step of 32 rows x 128 requests).  8192 x 8192 in groups of 64 with 96 requests
+// 48.0 -> 38.3 us; the linear layers of a Llama-3-8B block with 500 requests at p = 4 423 -> 331 us.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

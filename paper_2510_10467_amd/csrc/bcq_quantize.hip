@@ -220,8 +220,9 @@ __device__ __forceinline__ void greedy_plane(Lane &s)
 
 // The alternation stops early at a fixed point: a cycle is a function of the codes alone, so codes that come
 // out as they went in give the same scales and the same codes in every cycle that is left.  The lanes of a wave go on
-// together until none of their groups has changed a code (groups that have settled repeat themselves).  Normal weights
-// with a few outliers settle in a fraction of 20 cycles (4096 x 4096, p = 2 .. 4, T = 20: 446 -> 294 us).
+// together until none of their groups has changed a code (groups that have settled repeat themselves).  Of normal weights with a few
+// outliers a group of 128 needs 5 of 20 cycles in each stage on average, and the 16 groups of a wave run 8 to 11 (4096 x 4096, p =
+// 2 .. 4, T = 20: 446 -> 294 us when this came; now 245, and 399 without it, which is what weights that never settle would take).
 template <int P>
 __device__ __forceinline__ bool any_changed(const Lane &s, const uint32_t (&word)[P])
 {

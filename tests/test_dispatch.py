@@ -34,8 +34,8 @@ SUMMING_IS_AHEAD = [
 ]
 
 LEVEL_IS_AHEAD = [
-    ((3, 28672, 8192, 2048, 128, False), 1271.0, 963.0),
-    ((4, 8192, 8192, 96, 64, False), 51.0, 40.0),
+    ((3, 28672, 8192, 2048, 128, False), 1182.0, 917.0),
+    ((4, 8192, 8192, 96, 64, False), 48.0, 38.3),
     ((3, 8935, 8960, 211, 128, False), 103.0, 75.4),
     ((4, 5632, 26624, 189, 64, False), 195.7, 157.6),
     ((4, 3208, 16384, 365, 128, False), 127.5, 100.9),
