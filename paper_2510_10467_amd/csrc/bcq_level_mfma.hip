@@ -29,10 +29,13 @@
 //
 // What bounds it: on a full chip the matrix instructions with the look-ups between them (matrix pipe busy for 63 / 55 / 47 % of the
 // cycles at p = 2 / 3 / 4) and the clock, which random operands hold at 1.7 to 1.95 GHz (with activations of zero the same cycles
-// pass at 2.3 to 2.4): 28672 x 8192 with 2048 requests at p = 3 1182 -> 917 us = 1049 TFLOP/s, where the library's plain fp16
-// product of 8192^3 reaches 1210 (1750 with zeros).  Smaller tiles are bound by the look-ups (four matrix instructions of 32 cycles
-// and about 30 vector instructions of 4 per step of 32 rows x 128 requests).  8192 x 8192 in groups of 64 with 96 requests
-// 48.0 -> 38.3 us; the linear layers of a Llama-3-8B block with 500 requests at p = 4 423 -> 331 us.
+// pass at 2.3 to 2.4); the library's plain fp16 product of 8192^3 reaches 1210 TFLOP/s (1750 with zeros).  Smaller tiles were bound
+// by neither: leaving out the look-ups, three quarters of the matrix instructions or the operand reads changed nothing, while leaving out the
+// fetch of words and scales took a quarter off (4096 x 14336 with 500 requests at p = 4 on tiles of 128 x 256: 240 -> 164 us), because
+// every row, plane and pair of groups asked for a line of its own, twice (see fetch_block and load_window).  That halved (196 us there):
+// 28672 x 8192 with 2048 requests at p = 3 937 -> 887 us = 1085 TFLOP/s, the linear layers of a Llama-3-8B block with 500 requests
+// at p = 4 326 -> 301, 8192 x 8192 in groups of 64 with 96 requests 37.4 -> 34.4.  What the fetch still costs there is 30 us,
+// the barriers about 10.
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
@@ -199,10 +202,26 @@ struct Shape {
     static constexpr int THREADS = 64 * SW * TEAMS;
     static constexpr int TILE = REQS * kRowBytes;                   // one stage's activations
     static constexpr int XU = TILE / 1024 / SW;                     // loads of 1 KiB per wave and stage
-    static constexpr int LDS = TEAMS * kRing * TILE;
+    static constexpr int TILES = TEAMS * kRing * TILE;
     static_assert(XU * 1024 * SW == TILE && XU >= 1, "tile does not split over the team");
-    static_assert((TEAMS - 1) * SW * QT * 4096 <= LDS, "accumulator exchange must fit in the tiles");
-    static_assert(LDS <= 160 * 1024, "tiles must fit in LDS");
+    static_assert((TEAMS - 1) * SW * QT * 4096 <= TILES, "accumulator exchange must fit in the tiles");
+};
+
+// LDS of a kernel: the tiles, then what it takes for plane words to change lanes, then the scales of a window of columns.
+template <int P, typename S, bool OFFSET>
+struct Lds {
+    // (not with 256 requests, where the registers are needed, nor where two workgroups share a CU, nor where it leaves no room for the scales)
+    static constexpr bool COALESCE = S::QT < 8 && !(S::QT == 2 && S::WR == 4) && !(OFFSET && P == 4);
+    static constexpr int WAVES = S::TEAMS * S::SW;
+    static constexpr int HANDOVER = COALESCE ? 2048 : 0;            // per wave
+    static constexpr int SCALES_AT = S::TILES + WAVES * HANDOVER;
+    static constexpr int PLANES = P + (OFFSET ? 1 : 0);             // offsets are kept like another plane's scales
+    static constexpr int limit = S::QT == 2 && S::WR == 4 ? 80 * 1024 : 160 * 1024;
+    // bytes of a row's scales of one plane in LDS; at least those of two rounds in groups of 64
+    static constexpr int WINDOW = SCALES_AT + S::ROWS * PLANES * 64 <= limit ? 64 : SCALES_AT + S::ROWS * PLANES * 32 <= limit || S::TEAMS > 1 ? 32 : 16;
+    static constexpr int BYTES = SCALES_AT + S::ROWS * PLANES * WINDOW;
+    static_assert(BYTES <= 160 * 1024, "must fit in LDS");
+    static_assert(WINDOW >= 16 * S::TEAMS, "a window holds the scales of two rounds in groups of 64");
 };
 
 // the workgroup's rows (block rowblk of the matrix) and requests b0 .. b0 + nreq - 1
@@ -225,7 +244,6 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
     // rows and requests past the end repeat the last one (their results are not stored)
     const uint32_t my_row = min(row0 + r32, a.m - 1);
     uint32_t w_off = my_row * a.row_stride + half * 16;
-    uint32_t s_off = my_row * a.scale_row_stride + (a.gshift > 0 ? 0u : a.gshift < 0 ? half * 4u : half * 2u);
     const uint32_t s_pair = a.gshift > 0 ? 2u : a.gshift < 0 ? 8u : 4u;      // bytes of a row's scales per pair of groups
     // Load i of a stage brings the 1 KiB of requests 8i .. 8i+7; lane l delivers part (l & 7) ^ (request / 2 & 7) of request
     // 8i + (l >> 3).  Parts 0-3 are columns 32w .. of the pair's first group, 4-7 of its second.
@@ -244,24 +262,88 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
         __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (__attribute__((address_space(3))) void *)(xt + w * S::TILE + (k * SW + tw) * 1024), 16,
                                                  (int)xs_src[k], pair * 512 + w * 64, 0, 0);
     };
-    u32x4 word[P], word_n[P];
-    uint32_t sc[P], later[P], zc = 0, later_z = 0;
+    // What a fetch of plane words or scales costs is not its bytes but the lines it asks for, one per row: 16 bytes of the words and
+    // two of the scales of every row and plane, one pair of groups at a time, made 64 requests per load and moved a whole line
+    // into the CU for each, as much again as the activations.  So
+    //   scales       come for a window of columns at a time, straight into LDS, shared by the waves of the rows (128 x 256, 4096 x
+    //                14336 with 500 requests: 240 us with, 192 without the fetch of every pair's scales)
+    //   plane words  come for two pairs at a time, four neighbouring lanes on 64 bytes of a row (lane l: rows l / 4 and 16 + l / 4,
+    //                part l % 4), which the memory pipe takes as one request, and change lanes in LDS (COALESCE: another 10 %, of
+    //                which the LDS takes 4 back)
+    using M = Lds<P, S, OFFSET>;
+    constexpr bool COALESCE = M::COALESCE;
+    constexpr int WINDOW = M::WINDOW;
+    u32x4 word[P], later_word[P], word_n[P][COALESCE ? 2 : 1];
+    uint32_t sc[P], zc = 0;                 // scales and offset of the next pair: low half first, high half columns 64 .. (groups of 64)
 #pragma unroll
     for (int i = 0; i < P; ++i) sc[i] = 0;
-    auto fetch = [&](int pair) {
-        asm volatile("" : "+v"(w_off), "+v"(s_off));    // lane offsets stay 32 bits wide, in the load's own addressing mode
+    uint32_t wq_off[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) wq_off[j] = min(row0 + 16 * j + (lane >> 2), a.m - 1) * a.row_stride;
+    unsigned char *handover = lds + S::TILES + wave * M::HANDOVER;
+    // row r, part c at 64 r + 16 (c ^ (r / 4 & 3)): the 16 rows that a read takes at a time use all banks
+    unsigned char *put_at = handover + (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) * 16);
+    const unsigned char *get_at = handover + r32 * 64;
+    const int get_swz = (r32 >> 2) & 3;
+
+    // The teams take blocks of two neighbouring pairs in turn; what is left after whole rounds of blocks goes out as single pairs if there are
+    // no more of them than teams.
+    const int wpairs = WINDOW / (a.gshift > 0 ? 4 : (int)s_pair);       // pairs of a window
+    const int rounds = (a.npairs + TEAMS - 1) / TEAMS;
+    const int last = a.npairs - 1;
+    auto pair_of = [&](int it) { return (it >> 1) * (2 * TEAMS) + (it & 1) + (it == rounds - 1 && !(it & 1) ? team : 2 * team); };
+
+    auto fetch_direct = [&](int pair) {     // 16 bytes of the lane's own row
+        asm volatile("" : "+v"(w_off));     // lane offsets stay 32 bits wide, in the load's own addressing mode
 #pragma unroll
         for (int i = 0; i < P; ++i)
-            word_n[i] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + (uint32_t)pair * 32 + w_off);
-        const uint32_t col = (uint32_t)pair * s_pair;
-        if (a.gshift < 0) {
+            word_n[i][0] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + (uint32_t)pair * 32 + w_off);
+    };
+    auto fetch_block = [&](int pair) {      // the pair and its neighbour
+        // (past the end of a row: its last part, for a pair that is not there)
+        const uint32_t col = min((uint32_t)pair * 32 + (lane & 3) * 16, a.row_stride - 16);
 #pragma unroll
-            for (int i = 0; i < P; ++i) sc[i] = *reinterpret_cast<const uint32_t *>(a.scales + (size_t)i * a.scale_plane_stride + col + s_off);
-            if (OFFSET) zc = *reinterpret_cast<const uint32_t *>(a.offsets + col + s_off);
-        } else {
+        for (int j = 0; j < 2; ++j) {
+            uint32_t off = wq_off[j] + col;
+            asm volatile("" : "+v"(off));
 #pragma unroll
-            for (int i = 0; i < P; ++i) sc[i] = *reinterpret_cast<const unsigned short *>(a.scales + (size_t)i * a.scale_plane_stride + col + s_off);
-            if (OFFSET) zc = *reinterpret_cast<const unsigned short *>(a.offsets + col + s_off);
+            for (int i = 0; i < P; ++i) word_n[i][COALESCE ? j : 0] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + off);
+        }
+    };
+    // Window w of the scales of all the workgroup's rows, four bytes per lane.  Rows start at multiples of two bytes (groups of 256 columns) or
+    // four: a window begins at the multiple of four below, and in groups of 256 it is half of what it could be, so that nothing is cut off.
+    // (Past the end of a row the next one follows, past the end of the set nothing is read; neither is used.)
+    unsigned char *const scales_lds = lds + M::SCALES_AT;
+    const uint32_t wg_row0 = rowblk * S::ROWS;
+    const auto s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.scales), 0, (int)(((uint32_t)P * a.scale_plane_stride + 3) & ~3u), 0x00020000);
+    const auto z_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(OFFSET ? a.offsets : a.scales), 0, (int)((a.scale_plane_stride + 3) & ~3u), 0x00020000);
+    auto load_window = [&](int w) {
+        constexpr int PER_ROW = WINDOW / 4, ROWS = 64 / PER_ROW;        // lanes per row, rows per load
+        constexpr int PER_PLANE = S::ROWS / ROWS, LOADS = M::PLANES * PER_PLANE;
+        static_assert(S::ROWS % ROWS == 0, "a load covers rows of one plane");
+        const uint32_t col = (uint32_t)(w * wpairs) * s_pair;
+#pragma unroll 1
+        for (int j = wave; j < LOADS; j += M::WAVES) {
+            const int plane = j / PER_PLANE, row = j % PER_PLANE * ROWS + lane / PER_ROW;
+            const bool z = OFFSET && plane == P;
+            const uint32_t at = min(wg_row0 + row, a.m - 1) * a.scale_row_stride + col + (z ? 0u : (uint32_t)plane * a.scale_plane_stride);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(z ? z_rsrc : s_rsrc, (__attribute__((address_space(3))) void *)(scales_lds + j * 256), 4,
+                                                     (int)((at & ~3u) + (lane % PER_ROW) * 4), 0, 0, 0);
+        }
+    };
+    const unsigned char *sc_lane = scales_lds + (row0 - wg_row0 + r32) * WINDOW + (a.gshift > 0 ? 0 : a.gshift < 0 ? half * 4 : half * 2);
+    const uint32_t sc_row = my_row * a.scale_row_stride;
+    auto read_scales = [&](int pair) {      // of a pair in the window that is there
+        const unsigned char *at = sc_lane + (pair & (wpairs - 1)) * (int)s_pair;
+#pragma unroll
+        for (int i = 0; i < M::PLANES; ++i) {
+            const unsigned char *from = at + i * (S::ROWS * WINDOW);
+            uint32_t v;
+            if (a.gshift < 0) v = *reinterpret_cast<const uint32_t *>(from);
+            else if (a.gshift == 0) v = *reinterpret_cast<const unsigned short *>(from);
+            else v = *reinterpret_cast<const unsigned short *>(from + ((sc_row + (i < P ? (uint32_t)i * a.scale_plane_stride : 0u)) & 2));
+            if (i < P) sc[i < P ? i : 0] = v;
+            else zc = v;
         }
     };
 
@@ -279,17 +361,35 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
         for (int e = 0; e < 16; ++e) acc[q][e] = 0.f;
 
     L lev;
-    uint32_t codes[4];
-    auto begin_pair = [&]() {                   // the words and scales that fetch() brought become the current ones
+    uint32_t codes[4], later[P], later_z = 0;
+    auto begin_pair = [&]() {                   // the scales of the current pair become levels
         uint32_t first[P];
 #pragma unroll
         for (int i = 0; i < P; ++i) {
-            word[i] = word_n[i];
             first[i] = sc[i] & 0xffffu;
             later[i] = sc[i] >> 16;
         }
         later_z = zc >> 16;
         lev.form(first, zc & 0xffffu);
+    };
+    auto begin_block = [&]() {                  // the words that came for the next two pairs (COALESCE: through LDS to the lanes that use them)
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            if constexpr (COALESCE) {
+                *reinterpret_cast<u32x4 *>(put_at) = word_n[i][0];
+                *reinterpret_cast<u32x4 *>(put_at + 1024) = word_n[i][COALESCE ? 1 : 0];
+                word[i] = *reinterpret_cast<const u32x4 *>(get_at + ((half ^ get_swz) * 16));
+                later_word[i] = *reinterpret_cast<const u32x4 *>(get_at + (((2 + half) ^ get_swz) * 16));
+            } else {
+                word[i] = word_n[i][0];
+            }
+        }
+        begin_pair();
+    };
+    auto second_pair = [&]() {
+#pragma unroll
+        for (int i = 0; i < P; ++i) word[i] = COALESCE ? later_word[i] : word_n[i][0];
+        begin_pair();
     };
     auto make = [&](int t) {                    // weights of step t of a pair
         if (t == 8 && a.gshift < 0) lev.form(later, later_z);       // groups of 64: columns 64 .. of both groups
@@ -306,38 +406,49 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
         return __builtin_bit_cast(v8h, u32x4{d0, d1, d2, d3});
     };
 
-    const int last = a.npairs - 1;
-    if (team <= last) {
-        fetch(team);
+    if (pair_of(0) <= last) {
+        if constexpr (COALESCE) fetch_block(pair_of(0));
+        else fetch_direct(pair_of(0));
 #pragma unroll
         for (int w = 0; w < kRing - 1; ++w)
 #pragma unroll
-            for (int k = 0; k < XU; ++k) stage_unit(team, w, k);
+            for (int k = 0; k < XU; ++k) stage_unit(pair_of(0), w, k);
     }
+    load_window(0);
     asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
     v8h wb, xa[UT];
-    if (team <= last) {
-        begin_pair();
+    if (pair_of(0) <= last) {
+        read_scales(pair_of(0));
+        begin_block();
         wb = make(0);
 #pragma unroll
         for (int u = 0; u < UT; ++u) xa[u] = operand(0, u);
     }
-    const int rounds = (a.npairs + TEAMS - 1) / TEAMS;
-    for (int it = 0; it < rounds; ++it) {
-        const int pair = it * TEAMS + team;
+    // One pair of groups.  SECOND: of its block.
+    auto run_pair = [&](auto second, int it) {
+        constexpr bool SECOND = decltype(second)::value;
+        const int pair = pair_of(it);
         if (pair > last) {                      // a team without a pair of its own in the last round meets the barriers
             asm volatile("s_barrier\n\ts_barrier\n\ts_barrier\n\ts_barrier" ::: "memory");
-            continue;
+            return;
         }
-        const int npair = min(pair + TEAMS, last);                  // (past the end: something that is there, for nothing)
+        const int npair = min(pair_of(it + 1), last);               // (past the end: something that is there, for nothing)
+        constexpr int FETCHED = COALESCE ? (SECOND ? 0 : 2 * P) : P;        // loads of the words that come next
+        // the next pair opens a window: nobody needs the old one any more
+        const int nstart = ((it + 1) >> 1) * (2 * TEAMS);
+        if (SECOND && (nstart & (wpairs - 1)) == 0 && nstart <= last) load_window(nstart / wpairs);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < 16; ++t) {
             v8h wn, xn[UT];
-            if (t == 4) fetch(npair);
 #pragma unroll
             for (int k = 0; k < XU; ++k)
                 if (k * 4 / XU == (t & 3)) stage_unit(t < 4 ? pair : npair, ((t >> 2) + kRing - 1) & (kRing - 1), k);
-            if (t == 15) begin_pair();
+            if (t == 13) read_scales(npair);
+            if (t == 15) {
+                if constexpr (SECOND) begin_block();
+                else second_pair();
+            }
 #pragma unroll
             for (int c = 0; c < NC; ++c) {
                 const int tn = c + 1 < NC ? t : (t + 1) & 15, cn = c + 1 < NC ? c + 1 : 0;
@@ -362,9 +473,22 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
+            if (t == 3) {
+                // behind this stage's loads, so that two barriers can leave them under way
+                if constexpr (!COALESCE) fetch_direct(npair);
+                else if constexpr (!SECOND) fetch_block(min(pair_of(it + 2), last));
+                __builtin_amdgcn_sched_barrier(0);
+            }
             // what the step before the last barrier asked for has landed; what this stage asked for is still under way
-            if ((t & 3) == 3) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XU) : "memory");
+            if ((t & 3) == 3) {
+                if (t <= 7) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XU + FETCHED) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(XU) : "memory");
+            }
         }
+    };
+    for (int it = 0; it < rounds; it += 2) {
+        run_pair(std::false_type{}, it);
+        if (it + 1 < rounds) run_pair(std::true_type{}, it + 1);
     }
 
     if constexpr (TEAMS > 1) {
@@ -432,7 +556,8 @@ template <int P, typename S, bool OFFSET>
 hipError_t launch(LevelParams pr, hipStream_t stream)
 {
     auto kernel = level_mfma_kernel<P, S, OFFSET>;
-    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), S::LDS)) return e;
+    constexpr int kLds = Lds<P, S, OFFSET>::BYTES;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLds)) return e;
     uint32_t wgs = (pr.m + S::ROWS - 1) / S::ROWS;
     if (pr.nmat > 1) {
         // every matrix gets whole workgroups
@@ -443,7 +568,7 @@ hipError_t launch(LevelParams pr, hipStream_t stream)
         }
         for (int k = pr.nmat; k < BCQ_MAX_MULTI; ++k) pr.mat_blk0[k] = wgs;      // never reached
     }
-    hipLaunchKernelGGL(kernel, dim3(wgs, (unsigned)((pr.batch + S::REQS - 1) / S::REQS)), dim3(S::THREADS), S::LDS, stream, pr);
+    hipLaunchKernelGGL(kernel, dim3(wgs, (unsigned)((pr.batch + S::REQS - 1) / S::REQS)), dim3(S::THREADS), kLds, stream, pr);
     return hipGetLastError();
 }
 
@@ -461,18 +586,20 @@ hipError_t launch_shape(const LevelParams &pr, int p, bool offset, hipStream_t s
 // Shapes and what a grid of each costs: microseconds per 128 columns with 256 and with at most 128 workgroups on the chip (n = 4096),
 // p = 4 and p = 2.  A call costs its rounds of workgroups over the 256 CUs; a round that fills half of the chip is quicker by up to
 // a third, because with random operands the full one is held back by power (256 x 256, p = 2, per pair of groups: 7.6 us on 256
-// CUs, 5.6 on 128, and 5.3 on 256 with activations of zero).  start_us is the part of a round that does not shrink with the width: the
+// CUs, 5.6 on 128, and 5.3 on 256 with activations of zero).  full_p4z, half_p4z: sixteen levels (p = 4 with offsets), which take two look-ups
+// per byte; they stand where the summing form was last measured to be level (5289 x 11520 with 955 requests), although the form has
+// become about a tenth faster since.  start_us is the part of a round that does not shrink with the width: the
 // first three stages of activations have to arrive, the results to leave, the launch itself (4096 x 256 with 500 requests at
 // p = 4 on 128 x 128: 8.5 us, where an eighth of the columns' share of 4096 x 4096 would be 3).
 // The LDS of the tiles of 128 x 64 (64 KiB, and at most 116 registers) lets two of those workgroups share a CU, that of the others
 // one.  Large tiles rebuild a weight for more requests, small ones keep the CUs busy on short matrices and batches.
 struct LevelShape {
     int rows, reqs;
-    float full_p4, full_p2, half_p4, half_p2, start_us;
+    float full_p4, full_p2, half_p4, half_p2, start_us, full_p4z, half_p4z;
 };
-constexpr LevelShape kLevelShapes[kLevelShapeCount] = {{256, 256, 4.50f, 4.00f, 3.24f, 2.62f, 7.65f}, {128, 256, 3.00f, 2.53f, 2.59f, 1.91f, 5.25f},
-                                       {128, 128, 1.62f, 1.34f, 1.43f, 1.06f, 5.65f}, {64, 128, 1.07f, 0.97f, 0.92f, 0.81f, 6.15f},
-                                       {128, 64, 1.11f, 0.82f, 1.00f, 0.72f, 3.65f},  {64, 64, 0.69f, 0.56f, 0.67f, 0.47f, 4.65f}};
+constexpr LevelShape kLevelShapes[kLevelShapeCount] = {{256, 256, 4.30f, 3.86f, 3.28f, 2.53f, 8.2f, 4.95f, 3.56f}, {128, 256, 2.71f, 2.40f, 2.11f, 1.65f, 5.9f, 3.30f, 2.85f},
+                                       {128, 128, 1.46f, 1.29f, 1.22f, 0.97f, 6.4f, 1.78f, 1.57f}, {64, 128, 0.96f, 0.90f, 0.82f, 0.71f, 6.7f, 1.18f, 1.01f},
+                                       {128, 64, 0.98f, 0.76f, 0.89f, 0.63f, 4.0f, 1.22f, 1.10f},  {64, 64, 0.63f, 0.53f, 0.57f, 0.44f, 5.3f, 0.76f, 0.74f}};
 constexpr int kTwoPerCu = 4;        // 128 x 64
 
 }  // namespace
@@ -487,7 +614,8 @@ int level_mfma_cheapest(const GemmArgs &a, float &us)
     for (int k = 0; k < kLevelShapeCount; ++k) {
         const LevelShape &c = kLevelShapes[k];
         const float wgs = (float)((a.m + c.rows - 1) / c.rows) * (float)((a.batch + c.reqs - 1) / c.reqs);
-        const float full = p >= 3 ? c.full_p4 : c.full_p2, half = p >= 3 ? c.half_p4 : c.half_p2;
+        const bool sixteen = p == 4 && a.offsets[p];
+        const float full = sixteen ? c.full_p4z : p >= 3 ? c.full_p4 : c.full_p2, half = sixteen ? c.half_p4z : p >= 3 ? c.half_p4 : c.half_p2;
         const float rounds = __builtin_floorf(wgs / 256.f), rest = wgs / 256.f - rounds;
         float all = 32.f * (rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f)));
         // Two workgroups on a CU (4096 columns, p = 4: 256 of them take 36.9 us, 320 59.0, 512 64.0) on longer rows lose it again:
@@ -501,9 +629,8 @@ int level_mfma_cheapest(const GemmArgs &a, float &us)
             us = all;
         }
     }
-    // Sixteen levels (p = 4 with offsets) take two look-ups per byte: 1.08 to 1.2 times the time, where the summing form takes 1.0 to
-    // 1.02 times its own.  At p <= 2 the summing form takes about 1.05 times the time its prices say.
-    us *= p == 4 && a.offsets[p] ? 1.1f : p <= 2 ? 0.95f : 1.f;
+    // At p <= 2 the summing form takes about 1.05 times the time its prices say.
+    if (p <= 2) us *= 0.95f;
     return best;
 }
 

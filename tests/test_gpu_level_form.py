@@ -64,6 +64,27 @@ def test_every_weight_bit_for_bit(gpu, force, n, group, with_offsets):
             assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
 
 
+@pytest.mark.parametrize("n,group", [(256, 256), (2304, 256), (1280, 128), (4352, 64), (4352, 128)])
+@pytest.mark.parametrize("with_offsets", [False, True])
+def test_every_weight_over_several_windows_of_scales(gpu, force, n, group, with_offsets):
+    """Widths of 1, 5, 9 and 17 pairs of column groups: a last block of one pair, teams without one, windows of scales that end in the
+    middle of a row; 67 rows, so that in groups of 256 rows and planes of scales start at odd multiples of two bytes."""
+    import paper_2510_10467_amd as bcq
+    m = 67
+    layer = syn.make_layer(m, n, group=group, seed=(956, n, group), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = gpu.to_dev(np.eye(n, dtype=np.float16))
+    for p in (1, 2, 3, 4):
+        z = syn.make_offsets(p, m, n, group, seed=(957, n, p)) if with_offsets else None
+        z_dev = None if z is None else gpu.to_dev(z)
+        expected = (weights16(layer, p, group, z).T + np.float16(0)).view(np.uint16)
+        for shape in SHAPES[:6]:
+            force(shape)
+            y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x, group=group, offsets=z_dev)
+            wrong = np.argwhere((y + 0.0).cpu().numpy().view(np.uint16) != expected)
+            assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
+
+
 @pytest.mark.parametrize("shape", SHAPES)
 def test_products_that_are_exact(gpu, force, shape):
     """Scales of 1, 1/4, 1/16, 1/64 and whole activations up to 8: every partial sum is a multiple of 1/64 below 2^14 and therefore
