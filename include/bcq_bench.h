@@ -52,7 +52,8 @@ int bcq_selected_kernel(void);
  * for 256 requests and four row blocks served by two teams of waves that share the activation tiles; per-request
  * precision uses the row blocks and whether the tile has 32 requests only, beyond 64 requests the whole shape if it
  * has 64 requests or more.  (1, 100) .. (1, 105) force the level form (rows rebuilt by look-ups, n a multiple of 256,
- * uniform precision) with 256 x 256, 128 x 256, 128 x 128, 64 x 128, 128 x 64 and 64 x 64 rows x requests.  (0, 0) restores the automatic choice.  Returns 0, or -6 for any other pair.
+ * all but the first also for per-request precision from 33 requests on, per precision) with 256 x 256, 128 x 256, 128 x 128, 64 x 128, 128 x 64
+ * and 64 x 64 rows x requests.  (0, 0) restores the automatic choice.  Returns 0, or -6 for any other pair.
  */
 int bcq_select_dequant_shape(int request_tiles, int row_blocks);
 

@@ -6,7 +6,8 @@
 //                            own scales applied to the group sums
 //   dequant_mixed_kernel     per-request precision at 64 requests per workgroup: W_q rebuilt once per precision present
 //   dequant_byclass_kernel   per-request precision beyond 64 requests: the uniform kernel's body per precision, each
-//                            workgroup on the requests of its precision, picked out of the batch by rank
+//                            workgroup on the requests of its precision, picked out of the batch by rank (where the level
+//                            form's kernel of the same kind is not ahead, see level_classes)
 //
 // Large-batch kernel: dequantise W_p = sum_i alpha_i B_i tile by tile (Fig. 1(b): p-bit inference
 // reconstructs the weights from the first p planes and the scale set of precision p) and feed the
@@ -116,36 +117,6 @@ struct Ahead {
     uint32_t w[P];
 };
 
-// The requests of precision q (after clamping to [1, p_max]) in the order of the batch: those of rank b0 .. b0 + TB - 1
-// get their numbers written to req_of[0 .. TB - 1] by the workgroup's first wave; returns how many of these ranks
-// exist (0 or less: none), the same number in every wave, each of which runs the whole ranking itself.  Sixteen
-// independent loads at a time (1024 requests), so that a batch costs one memory latency, not one per 64 requests.
-template <int TB>
-__device__ __forceinline__ int rank_requests(const DequantParams &a, const int q, const int b0, uint32_t *req_of)
-{
-    const int lane = threadIdx.x & 63;
-    int seen = 0;                               // requests of precision q so far
-    for (int blk = 0; blk < a.batch && seen < b0 + TB; blk += 1024) {
-        int pv[16];
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int b = blk + 64 * j + lane;
-            pv[j] = b < a.batch ? a.p_req[b] : 0;
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int b = blk + 64 * j + lane;
-            const int pc = pv[j] < 1 ? 1 : (pv[j] > a.p_max ? a.p_max : pv[j]);
-            const bool is = b < a.batch && pc == q;
-            const unsigned long long mask = __ballot(is);
-            const int rank = seen + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-            if (is && rank >= b0 && rank < b0 + TB && threadIdx.x < 64) req_of[rank - b0] = (uint32_t)b;
-            seen += __popcll(mask);
-        }
-    }
-    return seen - b0 > TB ? TB : seen - b0;
-}
-
 // NT: 16-request tiles per workgroup (1, 2, 4, 8 or 16); TEAMS: teams of waves (K split inside the workgroup); RW: waves per
 // team = 16-row blocks per workgroup.
 // PW (plane-wise): instead of rebuilding W_p, the +-1.0 values from the table are themselves the matrix operand:
@@ -196,7 +167,7 @@ __device__ __forceinline__ void dequant_mfma_body(const DequantParams &a, const 
     int nreq = a.batch - b0;                  // requests from b0 on (may be more than the workgroup's 16 NT)
     const uint32_t *req_of = reinterpret_cast<const uint32_t *>(lds + lds_bytes(NT, LT));
     if constexpr (BYCLASS) {
-        nreq = rank_requests<16 * NT>(a, P, b0, reinterpret_cast<uint32_t *>(lds + lds_bytes(NT, LT)));
+        nreq = rank_requests<16 * NT>(a.p_req, a.batch, a.p_max, P, b0, reinterpret_cast<uint32_t *>(lds + lds_bytes(NT, LT)));
         if (nreq <= 0) return;                // (every wave of the workgroup: none has reached a barrier yet)
         __syncthreads();
     }
@@ -570,7 +541,7 @@ __device__ __forceinline__ void serve_precision(DequantParams a)
         // no scale set for this precision: its requests get zeros (the workgroup's rows of its tile of ranks)
         extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
         uint32_t *req_of = reinterpret_cast<uint32_t *>(lds + lds_bytes(NT, SHARE ? 1 : TEAMS));
-        const int nreq = rank_requests<16 * NT>(a, Q, (int)blockIdx.z * (16 * NT), req_of);
+        const int nreq = rank_requests<16 * NT>(a.p_req, a.batch, a.p_max, Q, (int)blockIdx.z * (16 * NT), req_of);
         if (nreq <= 0) return;
         __syncthreads();
         const uint32_t row0 = blockIdx.x * (16 * RW);
@@ -1457,6 +1428,48 @@ void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)
     row_blocks = rw;
 }
 
+// The requests that one precision is expected to have: an even split plus 1.3 standard deviations of a uniform draw (a precision that
+// gets a few requests more than its share should not need a second, nearly empty tile, which costs as much as a full one).
+static int expected_share(const GemmArgs &a, int &nsets, int &deepest)
+{
+    nsets = 0;
+    deepest = 1;
+    for (int q = 1; q <= a.p_max; ++q)
+        if (a.scales[q]) {
+            ++nsets;
+            deepest = q;
+        }
+    const float share = nsets ? (float)a.batch / (float)nsets : (float)a.batch;
+    return (int)__builtin_ceilf(share + 1.3f * __builtin_sqrtf(share * (float)(nsets > 1 ? nsets - 1 : 0) / (float)(nsets ? nsets : 1)));
+}
+
+// Per-request precision beyond 32 requests: whether the level form runs it, its body per precision (level_byclass_kernel), and on which shape.
+// Of 160 calls drawn where the dequantising kernels were the choice it is 1.4 to 1.5 times as fast on average (8192 x 8192 with 200 requests
+// 119 -> 63 us; up to 64 requests, where groups of 64 rule the plane-wise variant out, 1.2 to 1.6 times).
+static bool level_classes(const GemmArgs &a, int &shape)
+{
+    if (a.uniform_p != 0 || a.batch <= 32 || a.n % 256 != 0) return false;
+    int nsets, deepest;
+    GemmArgs share_of = a;
+    share_of.batch = expected_share(a, nsets, deepest);
+    if (nsets == 0) return false;
+    share_of.uniform_p = deepest;
+    float us = 0.f;
+    shape = level_mfma_cheapest_classes(share_of, nsets, us);
+    if (a.batch > kClassFrom && g_forced_level < 0) {
+        // The summing form per precision (dequant_byclass_kernel) keeps narrow matrices and short ones with few requests (16896 x 1280 with 311
+        // requests 37 against 43 us, 1826 x 7936 with 85 in groups of 64 30 against 41); 0.9 and 2 us: drawn calls took 0.77 to 1.5 times this.
+        int nt, rw;
+        const float all = 0.9f * 32.f * cheapest_shape(deepest, a.m, share_of.batch, 4, nt, rw, nsets);
+        const int rows = 16 * row_blocks_of(nt, rw);
+        const float rounds = __builtin_ceilf((float)((a.m + rows - 1) / rows) * (float)((share_of.batch + 16 * nt - 1) / (16 * nt)) * (float)nsets / 256.f);
+        const float start = 5.65f * rounds;
+        if (large_batch_us(all > start ? all : start, start, a.n) + (a.n < 4096 ? 0.f : 2.f) < us) return false;
+    }
+    if (g_forced_level >= 1) shape = g_forced_level;      // (256 x 256 is not among them)
+    return true;
+}
+
 bool dequant_mfma_supports(const GemmArgs &a)
 {
     // 32-bit byte offsets inside one plane / one scale plane / the activation matrix
@@ -1549,27 +1562,22 @@ hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool plane
                  : rw16 == 4 ? launch_planewise_mixed<1, 4, 4>(pr, a, stream)
                  : rw16 == 2 ? launch_planewise_mixed<1, 4, 2>(pr, a, stream) : launch_planewise_mixed<1, 4, 1>(pr, a, stream);
         }
+        // the precisions in the order the workgroups take them: the deepest first, those without a scale set last
+        int y = 0;
+        pr.class_order = 0;
+        for (int q = a.p_max; q >= 1; --q)
+            if (a.scales[q]) pr.class_order |= (uint32_t)q << (8 * y++);
+        for (int q = a.p_max; q >= 1; --q)
+            if (!a.scales[q]) pr.class_order |= (uint32_t)q << (8 * y++);
+        int level = 0;
+        if (g_forced_nt == 0 && level_classes(a, level)) return level_mfma_launch_classes(a, pr.class_order, level, stream);
         if (a.batch > kClassFrom && (g_forced_nt == 0 || g_forced_nt >= 4)) {
-            // Beyond 64 requests: the uniform kernel's body per precision, each on the requests of that precision
-            // wherever they sit in the batch (dequant_byclass_kernel).  A weight is then rebuilt once per
+            // Beyond 64 requests on widths the level form does not take: the uniform kernel's body per precision, each on the requests of that
+            // precision wherever they sit in the batch (dequant_byclass_kernel).  A weight is then rebuilt once per
             // precision and up to 256 requests, at the cost of that precision alone, instead of once per 64
             // requests at the cost of all precisions present.
-            int nsets = 0, y = 0;
-            pr.class_order = 0;
-            for (int q = a.p_max; q >= 1; --q)
-                if (a.scales[q]) {
-                    ++nsets;
-                    pr.class_order |= (uint32_t)q << (8 * y++);
-                }
-            for (int q = a.p_max; q >= 1; --q)
-                if (!a.scales[q]) pr.class_order |= (uint32_t)q << (8 * y++);
-            // an even split plus 1.3 standard deviations of a uniform draw: a precision that gets a few requests more
-            // than its share should not need a second, nearly empty tile (which costs as much as a full one)
-            const float share = nsets ? (float)a.batch / (float)nsets : (float)a.batch;
-            const int expected = (int)__builtin_ceilf(share + 1.3f * __builtin_sqrtf(share * (float)(nsets > 1 ? nsets - 1 : 0) / (float)(nsets ? nsets : 1)));
-            int deepest = 1;
-            for (int q = 1; q <= a.p_max; ++q)
-                if (a.scales[q]) deepest = q;
+            int nsets, deepest;
+            const int expected = expected_share(a, nsets, deepest);
             return launch_classes(pr, a, expected, nsets, deepest, stream);
         }
         // 64, 32 or 16 rows per workgroup by the same two-factor cost as the uniform kernel (measured with three

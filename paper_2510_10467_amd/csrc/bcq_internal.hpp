@@ -36,6 +36,36 @@ __device__ __forceinline__ int request_precision(const GemmArgs &a, int b)
     return a.scales[p] ? p : 0;
 }
 
+// The requests of precision q (after clamping to [1, p_max]) in the order of the batch: those of rank b0 .. b0 + TB - 1
+// get their numbers written to req_of[0 .. TB - 1] by the workgroup's first wave; returns how many of these ranks
+// exist (0 or less: none), the same number in every wave, each of which runs the whole ranking itself.  Sixteen
+// independent loads at a time (1024 requests), so that a batch costs one memory latency, not one per 64 requests.
+template <int TB>
+__device__ __forceinline__ int rank_requests(const int32_t *p_req, const int batch, const int p_max, const int q, const int b0, uint32_t *req_of)
+{
+    const int lane = threadIdx.x & 63;
+    int seen = 0;                               // requests of precision q so far
+    for (int blk = 0; blk < batch && seen < b0 + TB; blk += 1024) {
+        int pv[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int b = blk + 64 * j + lane;
+            pv[j] = b < batch ? p_req[b] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int b = blk + 64 * j + lane;
+            const int pc = pv[j] < 1 ? 1 : (pv[j] > p_max ? p_max : pv[j]);
+            const bool is = b < batch && pc == q;
+            const unsigned long long mask = __ballot(is);
+            const int rank = seen + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+            if (is && rank >= b0 && rank < b0 + TB && threadIdx.x < 64) req_of[rank - b0] = (uint32_t)b;
+            seen += __popcll(mask);
+        }
+    }
+    return seen - b0 > TB ? TB : seen - b0;
+}
+
 // More than 64 KiB of dynamic LDS needs a per-function attribute.  It sticks to the function, so it is set once per
 // kernel instance and device (and again only if a later launch asks for more); defined in bcq_api.hip.
 hipError_t allow_dynamic_lds(const void *kernel, int bytes);
@@ -76,6 +106,10 @@ constexpr int kLevelShapeCount = 6;
 bool level_mfma_supports(const GemmArgs &a);
 // its cheapest shape for a product, and what that one is expected to take in microseconds
 int level_mfma_cheapest(const GemmArgs &a, float &us);
+// Per-request precision: the same body per precision, each workgroup on the requests of one precision.  a: the call, with uniform_p the
+// deepest precision and batch the requests that a precision is expected to have; nsets: that many precisions.
+int level_mfma_cheapest_classes(const GemmArgs &a, int nsets, float &us);
+hipError_t level_mfma_launch_classes(const GemmArgs &a, uint32_t class_order, int shape, hipStream_t stream);
 // The estimate of both large-batch forms: `at_4096` is what a product of 4096 columns takes, of which `start` does not depend
 // on the width (beyond 4096 columns it no longer counts).
 inline float large_batch_us(float at_4096, float start, int64_t n)

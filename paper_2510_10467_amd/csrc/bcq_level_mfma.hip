@@ -27,6 +27,10 @@
 // A workgroup is TEAMS teams of WR x WQ waves; the teams take alternate pairs of groups with tiles of their own and meet at
 // the end (short matrices: rows alone do not fill the chip).
 //
+// Per-request precision (level_byclass_kernel): the same body per precision in one launch, each workgroup on the requests of its precision; a
+// weight is rebuilt once per precision and tile of requests by look-ups of that precision instead of by sums: 8192 x 8192 with 200
+// requests at precisions from {2, 3, 4} 119 -> 63 us (on 128 x 96: a third of 200 requests fills two tiles of 64 badly, one of 128 half).
+//
 // What bounds it: on a full chip the matrix instructions with the look-ups between them (matrix pipe busy for 63 / 55 / 47 % of the
 // cycles at p = 2 / 3 / 4) and the clock, which random operands hold at 1.7 to 1.95 GHz (with activations of zero the same cycles
 // pass at 2.3 to 2.4); the library's plain fp16 product of 8192^3 reaches 1210 TFLOP/s (1750 with zeros).  Smaller tiles were bound
@@ -65,6 +69,11 @@ struct LevelParams {
     uint32_t m;
     int batch, npairs;                      // npairs: pairs of 128-column groups
     int gshift;                             // scale groups of 64 (-1), 128 (0) or 256 (+1) columns
+    // per-request precision: a scale / offset set per precision, nullptr where there is none
+    const unsigned char *scale_sets[kMaxP + 1], *offset_sets[kMaxP + 1];
+    const int32_t *p_req;
+    int p_max;
+    uint32_t class_order;                   // byte y: the precision served by the workgroups with blockIdx.y = y
     // several matrices in one launch (nmat > 1): matrix k owns the workgroup rows mat_blk0[k] .. mat_blk0[k+1]-1
     int nmat;
     const unsigned char *mat_planes[BCQ_MAX_MULTI];
@@ -225,8 +234,10 @@ struct Lds {
 };
 
 // the workgroup's rows (block rowblk of the matrix) and requests b0 .. b0 + nreq - 1
-template <int P, typename S, bool OFFSET>
-__device__ __forceinline__ void level_body(const LevelParams &a, const int b0, const int nreq, const uint32_t rowblk)
+// BYCLASS (per-request precision): the requests of precision P of rank b0 .. b0 + S::REQS - 1 among them instead; every wave ranks the batch
+// itself, the numbers pass through LDS before the tiles need it and wait in registers until the results are stored.
+template <int P, typename S, bool OFFSET, bool BYCLASS = false>
+__device__ __forceinline__ void level_body(const LevelParams &a, const int b0, int nreq, const uint32_t rowblk)
 {
     constexpr int QT = S::QT, TEAMS = S::TEAMS, XU = S::XU, SW = S::SW;
     constexpr int UT = QT < 4 ? QT : 4;       // request tiles whose operands are held at a time
@@ -241,6 +252,17 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
     unsigned char *xt = lds + team * kRing * S::TILE;
     const uint32_t row0 = rowblk * S::ROWS + wr * 32;
 
+    uint32_t *const req_of = reinterpret_cast<uint32_t *>(lds);
+    constexpr int NL = (S::REQS + 63) / 64;
+    uint32_t listed[NL];
+    if constexpr (BYCLASS) {
+        nreq = rank_requests<S::REQS>(a.p_req, a.batch, a.p_max, P, b0, req_of);
+        if (nreq <= 0) return;                // (every wave of the workgroup: none has reached a barrier yet)
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NL; ++k) listed[k] = req_of[min(64 * k + lane, nreq - 1)];
+    }
+
     // rows and requests past the end repeat the last one (their results are not stored)
     const uint32_t my_row = min(row0 + r32, a.m - 1);
     uint32_t w_off = my_row * a.row_stride + half * 16;
@@ -252,9 +274,10 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
     for (int k = 0; k < XU; ++k) {
         const int req = 8 * (k * SW + tw) + (lane >> 3);
         const int part = (lane & 7) ^ ((req >> 1) & 7);
-        const uint32_t source = (uint32_t)(b0 + min(req, nreq - 1));
+        const uint32_t source = BYCLASS ? req_of[min(req, nreq - 1)] : (uint32_t)(b0 + min(req, nreq - 1));
         xs_src[k] = source * a.x_stride + (part >> 2) * 256 + (part & 3) * 16;
     }
+    if constexpr (BYCLASS) __syncthreads();   // the list has been read: its place belongs to the tiles
     // (buffer loads: the compiler counts loads of the global kind that write LDS among the LDS reads under way as well, and
     // then waits for all of those reads wherever it needs one)
     const auto x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.x), 0, (int)((uint32_t)a.batch * a.x_stride), 0x00020000);
@@ -519,6 +542,13 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
                 }
     }
 
+    // the list back into LDS, a copy per wave, where the scales were (the last barrier is behind all their readers)
+    uint32_t *const out_req = reinterpret_cast<uint32_t *>(scales_lds) + wave * (64 * NL);
+    if constexpr (BYCLASS) {
+        static_assert(M::WAVES * 256 * NL <= S::ROWS * M::PLANES * WINDOW, "the list must fit");
+#pragma unroll
+        for (int k = 0; k < NL; ++k) out_req[64 * k + lane] = listed[k];
+    }
     // element e of a tile: request 8 (e / 4) + 4 half + e % 4 of row r32
     const uint32_t row = row0 + r32;
     if (row < a.m) {
@@ -527,7 +557,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, c
 #pragma unroll
             for (int e = 0; e < 16; ++e) {
                 const int r = 32 * (wq * QT + q) + 8 * (e / 4) + 4 * half + (e % 4);
-                if (r < nreq) a.y[(size_t)(b0 + r) * a.m + row] = (_Float16)acc[q][e];
+                if (r < nreq) a.y[(size_t)(BYCLASS ? out_req[r] : (uint32_t)(b0 + r)) * a.m + row] = (_Float16)acc[q][e];
             }
     }
 }
@@ -550,6 +580,57 @@ __global__ __launch_bounds__(S::THREADS) void level_mfma_kernel(LevelParams a)
     }
     const int b0 = (int)blockIdx.y * S::REQS;
     level_body<P, S, OFFSET>(a, b0, min(S::REQS, a.batch - b0), wg);
+}
+
+// Per-request precision: byte blockIdx.y of class_order is the precision that a workgroup serves, blockIdx.z its tile of ranks (the slowest
+// dimension, so that the tiles that hold the work go first, as in the summing form's kernel).
+template <int Q, typename S>
+__device__ __forceinline__ void serve_precision(LevelParams a)
+{
+    if (!a.scale_sets[Q]) {
+        // no scale set for this precision: its requests get zeros
+        extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+        uint32_t *req_of = reinterpret_cast<uint32_t *>(lds);
+        const int nreq = rank_requests<S::REQS>(a.p_req, a.batch, a.p_max, Q, (int)blockIdx.z * S::REQS, req_of);
+        if (nreq <= 0) return;
+        __syncthreads();
+        for (int i = threadIdx.x; i < nreq * S::ROWS; i += S::THREADS) {
+            const uint32_t row = blockIdx.x * S::ROWS + (uint32_t)(i % S::ROWS);
+            if (row < a.m) a.y[(size_t)req_of[i / S::ROWS] * a.m + row] = (_Float16)0.f;
+        }
+        return;
+    }
+    a.scales = a.scale_sets[Q];
+    a.offsets = a.offset_sets[Q];
+    if (a.offsets) level_body<Q, S, true, true>(a, (int)blockIdx.z * S::REQS, 0, blockIdx.x);
+    else level_body<Q, S, false, true>(a, (int)blockIdx.z * S::REQS, 0, blockIdx.x);
+}
+
+template <typename S>
+__global__ __launch_bounds__(S::THREADS) void level_byclass_kernel(LevelParams a)
+{
+    switch ((a.class_order >> (8 * blockIdx.y)) & 0xffu) {
+    case 1: serve_precision<1, S>(a); break;
+    case 2: serve_precision<2, S>(a); break;
+    case 3: serve_precision<3, S>(a); break;
+    default: serve_precision<4, S>(a); break;
+    }
+}
+
+template <typename S>
+hipError_t launch_byclass(const LevelParams &pr, hipStream_t stream)
+{
+    auto kernel = level_byclass_kernel<S>;
+    constexpr int kWith = Lds<4, S, true>::BYTES > Lds<3, S, true>::BYTES ? Lds<4, S, true>::BYTES : Lds<3, S, true>::BYTES;
+    constexpr int kWithout = Lds<4, S, false>::BYTES > Lds<3, S, false>::BYTES ? Lds<4, S, false>::BYTES : Lds<3, S, false>::BYTES;
+    constexpr int kTwo = Lds<2, S, true>::BYTES > Lds<2, S, false>::BYTES ? Lds<2, S, true>::BYTES : Lds<2, S, false>::BYTES;
+    constexpr int kOne = Lds<1, S, true>::BYTES > Lds<1, S, false>::BYTES ? Lds<1, S, true>::BYTES : Lds<1, S, false>::BYTES;
+    constexpr int kMost = kWith > kWithout ? kWith : kWithout, kLess = kTwo > kOne ? kTwo : kOne;
+    constexpr int kLds = kMost > kLess ? kMost : kLess;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLds)) return e;
+    hipLaunchKernelGGL(kernel, dim3((pr.m + S::ROWS - 1) / S::ROWS, (unsigned)pr.p_max, (unsigned)((pr.batch + S::REQS - 1) / S::REQS)), dim3(S::THREADS),
+                       kLds, stream, pr);
+    return hipGetLastError();
 }
 
 template <int P, typename S, bool OFFSET>
@@ -600,41 +681,76 @@ struct LevelShape {
 constexpr LevelShape kLevelShapes[kLevelShapeCount] = {{256, 256, 4.30f, 3.86f, 3.28f, 2.53f, 8.2f, 4.95f, 3.56f}, {128, 256, 2.71f, 2.40f, 2.11f, 1.65f, 5.9f, 3.30f, 2.85f},
                                        {128, 128, 1.46f, 1.29f, 1.22f, 0.97f, 6.4f, 1.78f, 1.57f}, {64, 128, 0.96f, 0.90f, 0.82f, 0.71f, 6.7f, 1.18f, 1.01f},
                                        {128, 64, 0.98f, 0.76f, 0.89f, 0.63f, 4.0f, 1.22f, 1.10f},  {64, 64, 0.63f, 0.53f, 0.57f, 0.44f, 5.3f, 0.76f, 0.74f}};
-constexpr int kTwoPerCu = 4;        // 128 x 64
+// 128 x 96, for the requests of one precision of a batch
+constexpr LevelShape kLevel96 = {128, 96, 1.25f, 1.08f, 1.08f, 0.82f, 6.2f, 1.55f, 1.38f};
 
 }  // namespace
 
 // whole pairs of 128-column groups; 32-bit byte offsets are the caller's condition (dequant_mfma_supports)
 bool level_mfma_supports(const GemmArgs &a) { return a.uniform_p >= 1 && a.uniform_p <= kMaxP && a.n % 256 == 0; }
 
-int level_mfma_cheapest(const GemmArgs &a, float &us)
+namespace {
+
+// What a product is expected to take on a shape; times > 0: that many products of this size in one launch, one per precision.
+float shape_us(const LevelShape &c, const GemmArgs &a, int times)
 {
     const int p = a.uniform_p;
+    const bool classes = times > 0;
+    const float wgs = (float)((a.m + c.rows - 1) / c.rows) * (float)((a.batch + c.reqs - 1) / c.reqs) * (float)(classes ? times : 1);
+    const bool sixteen = p == 4 && a.offsets[p];
+    const float full = sixteen ? c.full_p4z : p >= 3 ? c.full_p4 : c.full_p2, half = sixteen ? c.half_p4z : p >= 3 ? c.half_p4 : c.half_p2;
+    const float rounds = __builtin_floorf(wgs / 256.f), rest = wgs / 256.f - rounds;
+    float all = 32.f * (rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f)));
+    float start = c.start_us * __builtin_ceilf(wgs / 256.f);
+    if (classes) {
+        // Per-request precision: every precision at the price of the deepest comes out a seventh too high, and a workgroup ranks the
+        // batch before anything else.
+        const float rank_us = 2.5f;
+        all *= 0.87f;
+        start = (c.start_us + rank_us) * __builtin_ceilf(wgs / 256.f);
+        return large_batch_us(all > start ? all : start, start, a.n) + (a.n < 4096 ? 0.f : rank_us);
+    }
+    // Two workgroups on a CU (4096 columns, p = 4: 256 of them take 36.9 us, 320 59.0, 512 64.0) on longer rows lose it again:
+    // a lane reads 16 bytes of a row at a time, and the lines of that many rows do not stay in L2 from one read to the next
+    // (21248 x 8192 with 587 requests at p = 4: 1.7 times what 4096 columns would let one expect).
+    if (c.rows == 128 && c.reqs == 64 && wgs > 256.f && a.n <= 4096) all *= 0.85f;
+    return large_batch_us(all, start, a.n);
+}
+
+}  // namespace
+
+int level_mfma_cheapest(const GemmArgs &a, float &us)
+{
     int best = -1;
     for (int k = 0; k < kLevelShapeCount; ++k) {
-        const LevelShape &c = kLevelShapes[k];
-        const float wgs = (float)((a.m + c.rows - 1) / c.rows) * (float)((a.batch + c.reqs - 1) / c.reqs);
-        const bool sixteen = p == 4 && a.offsets[p];
-        const float full = sixteen ? c.full_p4z : p >= 3 ? c.full_p4 : c.full_p2, half = sixteen ? c.half_p4z : p >= 3 ? c.half_p4 : c.half_p2;
-        const float rounds = __builtin_floorf(wgs / 256.f), rest = wgs / 256.f - rounds;
-        float all = 32.f * (rounds * full + (rest == 0.f ? 0.f : rest <= 0.5f ? half : half + (full - half) * (2.f * rest - 1.f)));
-        // Two workgroups on a CU (4096 columns, p = 4: 256 of them take 36.9 us, 320 59.0, 512 64.0) on longer rows lose it again:
-        // a lane reads 16 bytes of a row at a time, and the lines of that many rows do not stay in L2 from one read to the next
-        // (21248 x 8192 with 587 requests at p = 4: 1.7 times what 4096 columns would let one expect).
-        if (k == kTwoPerCu && wgs > 256.f && a.n <= 4096) all *= 0.85f;
-        const float start = c.start_us * __builtin_ceilf(wgs / 256.f);
-        all = large_batch_us(all, start, a.n);
+        const float all = shape_us(kLevelShapes[k], a, 0);
         if (best < 0 || all < us) {
             best = k;
             us = all;
         }
     }
     // At p <= 2 the summing form takes about 1.05 times the time its prices say.
-    if (p <= 2) us *= 0.95f;
+    if (a.uniform_p <= 2) us *= 0.95f;
     return best;
 }
 
-hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count)
+int level_mfma_cheapest_classes(const GemmArgs &a, int nsets, float &us)
+{
+    int best = -1;
+    for (int k = 1; k <= kLevelShapeCount; ++k) {
+        const float all = shape_us(k < kLevelShapeCount ? kLevelShapes[k] : kLevel96, a, nsets);
+        if (best < 0 || all < us) {
+            best = k;
+            us = all;
+        }
+    }
+    if (a.n < 3072) us *= 1.15f;        // (drawn calls took 0.99 to 1.28 times the estimate there, 0.79 to 1.09 times beyond)
+    return best;
+}
+
+namespace {
+
+LevelParams level_params(const GemmArgs &a)
 {
     LevelParams pr{};
     pr.planes = reinterpret_cast<const unsigned char *>(a.planes);
@@ -649,6 +765,35 @@ hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, c
     pr.m = (uint32_t)a.m;
     pr.batch = a.batch;
     pr.npairs = (int)(a.n / 256);
+    return pr;
+}
+
+}  // namespace
+
+hipError_t level_mfma_launch_classes(const GemmArgs &a, uint32_t class_order, int shape, hipStream_t stream)
+{
+    LevelParams pr = level_params(a);
+    for (int q = 1; q <= kMaxP; ++q) {
+        pr.scale_sets[q] = reinterpret_cast<const unsigned char *>(a.scales[q]);
+        pr.offset_sets[q] = a.scales[q] ? reinterpret_cast<const unsigned char *>(a.offsets[q]) : nullptr;
+    }
+    pr.p_req = a.p_req;
+    pr.p_max = a.p_max;
+    pr.class_order = class_order;
+    switch (shape) {
+    case 1: return launch_byclass<Shape<4, 4, 2, 1>>(pr, stream);
+    case 2: return launch_byclass<Shape<4, 4, 1, 2>>(pr, stream);
+    case 3: return launch_byclass<Shape<4, 2, 1, 2>>(pr, stream);
+    case 4: return launch_byclass<Shape<2, 4, 1, 2>>(pr, stream);
+    case 5: return launch_byclass<Shape<2, 2, 1, 4>>(pr, stream);
+    case 6: return launch_byclass<Shape<3, 4, 1, 2>>(pr, stream);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, const GemmArgs *mats, int count)
+{
+    LevelParams pr = level_params(a);
     pr.scales = reinterpret_cast<const unsigned char *>(a.scales[a.uniform_p]);
     const bool offset = a.offsets[a.uniform_p] != nullptr;
     pr.offsets = reinterpret_cast<const unsigned char *>(a.offsets[a.uniform_p]);

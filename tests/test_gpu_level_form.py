@@ -111,6 +111,58 @@ def test_products_that_are_exact(gpu, force, shape):
         assert torch.equal(y, bcq.bcq_gemv(other, dl.scales[p], p, x)), f"shape {shape} p={p}: planes >= p influenced the result"
 
 
+@pytest.mark.parametrize("shape", [(1, 101), (1, 102), (1, 103), (1, 104), (1, 105), (0, 0)])
+@pytest.mark.parametrize("m,n,batch,group", [(150, 1280, 33, 128), (70, 768, 129, 64), (259, 1536, 300, 256)])
+def test_per_request_precision(gpu, force, shape, m, n, batch, group):
+    """The form per precision, its requests wherever they sit in the batch: with offsets for some precisions and without, a precision without
+    a scale set (zeros), precisions out of range (clamped), all requests at one precision, a ragged last tile of rows and of requests."""
+    layer = syn.make_layer(m, n, group=group, seed=(960, m, n), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = syn.make_x(batch, n, seed=(961, batch))
+    p_req = syn.make_p_req(batch, 1, 4, seed=(962, batch))
+    some = {q: syn.make_offsets(q, m, n, group, seed=(963, q)) for q in (2, 4)}
+    for req in (p_req, np.full(batch, 3, dtype=np.int32)):
+        for z in (None, some):
+            force(shape)
+            used, _ = gpu.check_mixed(dl, req, x, "dequant_mfma", group, offsets_by_p=z)
+            assert used == "dequant_mfma"
+    import paper_2510_10467_amd as bcq
+    force(shape)
+    x_dev = gpu.to_dev(x)
+    y = bcq.bcq_gemm_mixed(dl.planes, dl.scales, gpu.to_dev(p_req), x_dev, group=group).cpu().numpy()
+    outside = np.where(p_req == 1, -3, np.where(p_req == 4, 9, p_req)).astype(np.int32)
+    assert np.array_equal(y, bcq.bcq_gemm_mixed(dl.planes, dl.scales, gpu.to_dev(outside), x_dev, group=group).cpu().numpy())
+    del dl.scales[2]
+    z = bcq.bcq_gemm_mixed(dl.planes, dl.scales, gpu.to_dev(p_req), x_dev, group=group).cpu().numpy()
+    assert not z[p_req == 2].any() and np.array_equal(z[p_req != 2], y[p_req != 2])
+
+
+def test_per_request_precision_on_tiles_of_96(gpu):
+    """Sizes that the automatic choice gives 128 rows x 96 requests; capture in a graph and replays give what the call gives."""
+    import torch
+
+    import paper_2510_10467_amd as bcq
+    m, n, batch = 6000, 512, 255
+    layer = syn.make_layer(m, n, seed=(964, m), precisions=[2, 3, 4], signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = syn.make_x(batch, n, seed=(964, batch))
+    p_req = syn.make_p_req(batch, 2, 4, seed=(964, 0))
+    used, _ = gpu.check_mixed(dl, p_req, x, "auto")
+    assert used == "dequant_mfma"
+    x_dev, r_dev = gpu.to_dev(x), gpu.to_dev(p_req)
+    eager = bcq.bcq_gemm_mixed(dl.planes, dl.scales, r_dev, x_dev)
+    y = torch.empty_like(eager)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bcq.bcq_gemm_mixed(dl.planes, dl.scales, r_dev, x_dev, y=y)
+    for other in (p_req, np.roll(p_req, 7), np.full(batch, 4, dtype=np.int32)):
+        r_dev.copy_(gpu.to_dev(other))
+        y.fill_(0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, bcq.bcq_gemm_mixed(dl.planes, dl.scales, r_dev, x_dev))
+
+
 @pytest.mark.parametrize("group", [64, 256])
 @pytest.mark.parametrize("shape", [(1, 2), (2, 4), (4, 40), (2, 8)])
 def test_summing_form_where_the_level_form_is_the_default(gpu, force, group, shape):
