@@ -1,6 +1,8 @@
 """ctypes binding of the C ABI in ``include/bcq.h``.
 
 Argument marshalling only: every step of the product runs in the HIP kernels.
+The product calls are marshalled by ``_bcq_host`` (``csrc/bcq_host.cpp``) where everything about a call is as it should
+be; the Python code below is what makes the other calls, or says what is wrong with them.
 PyTorch supplies device memory and the current stream.  There is no CPU
 fallback: if the shared library is missing the import of this module's
 functions raises, and every call checks that its tensors live on the GPU.
@@ -15,6 +17,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libbcq_hip.so")
 _lib = None
+_host = None
 
 BCQ_MAX_PLANES = 8
 KERNEL_AUTO, KERNEL_SIGN_SELECT, KERNEL_PLANE_MFMA, KERNEL_DEQUANT_MFMA = 0, 1, 2, 3
@@ -29,7 +32,7 @@ class BcqError(RuntimeError):
 
 def lib() -> ctypes.CDLL:
     """Load ``libbcq_hip.so`` (built in-tree by ``build.py``); fail loudly if absent."""
-    global _lib
+    global _lib, _host
     if _lib is None:
         if not os.path.exists(_LIB_PATH):
             raise ImportError(
@@ -66,6 +69,9 @@ def lib() -> ctypes.CDLL:
         for f in (L.bcq_select_kernel, L.bcq_pack, L.bcq_unpack, L.bcq_gemv, L.bcq_gemm_mixed, L.bcq_gemv_offset,
                   L.bcq_gemm_mixed_offset):
             f.restype = i32
+        from . import _bcq_host
+        _bcq_host.bind(*(ctypes.cast(f, vp).value for f in (L.bcq_gemv_offset, L.bcq_gemv_multi, L.bcq_gemm_mixed, L.bcq_gemm_mixed_offset)), BcqError)
+        _host = _bcq_host
         _lib = L
     return _lib
 
@@ -136,6 +142,11 @@ def bcq_gemv(planes: torch.Tensor, scales_p: torch.Tensor, p: int, x: torch.Tens
              y: torch.Tensor | None = None, group: int = 128, offsets: torch.Tensor | None = None) -> torch.Tensor:
     """Uniform precision: y[b][r] = sum_{i<p} sum_j scales_p[i][r][j/group] * B_i[r][j] * x[b][j];
     with ``offsets`` (float16 [m][n/group], asymmetric scheme) plus sum_j offsets[r][j/group] * x[b][j]."""
+    if _host is None:
+        lib()
+    done = _host.gemv(planes, scales_p, p, x, y, group, offsets)
+    if done is not None:
+        return done
     _, m, words = planes.shape
     n = words * 32
     batch = x.shape[0]
@@ -162,6 +173,12 @@ def bcq_gemv_multi(planes: list, scales_p: list, p: int, x: torch.Tensor, ys: li
     """Several matrices (same n and precision) applied to the same activations in one call: the q/k/v or
     gate/up projections of a decoder layer.  Returns the list of outputs (those of bcq_gemv within the tolerance both are held
     to; bit for bit wherever the same kernel form serves both)."""
+    if ys is None:
+        if _host is None:
+            lib()
+        done = _host.gemv_multi(planes, scales_p, p, x, group)
+        if done is not None:
+            return done
     count = len(planes)
     batch, n = x.shape
     if len(scales_p) != count or (ys is not None and len(ys) != count):
@@ -191,6 +208,11 @@ def bcq_gemm_mixed(planes: torch.Tensor, scales_by_p: dict, p_req: torch.Tensor,
                    y: torch.Tensor | None = None, group: int = 128, offsets_by_p: dict | None = None) -> torch.Tensor:
     """Per-request precision: request b uses planes 0..p_req[b]-1 and scale set scales_by_p[p_req[b]]
     (and the offset set offsets_by_p[p_req[b]] if there is one)."""
+    if _host is None:
+        lib()
+    done = _host.gemm_mixed(planes, scales_by_p, p_req, x, y, group, offsets_by_p)
+    if done is not None:
+        return done
     p_max, m, words = planes.shape
     n = words * 32
     batch = x.shape[0]

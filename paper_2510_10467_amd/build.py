@@ -1,14 +1,17 @@
-"""Builds the HIP library in-tree: csrc/*.hip -> libbcq_hip.so for gfx950."""
+"""Builds in-tree: csrc/*.hip -> libbcq_hip.so for gfx950, and csrc/bcq_host.cpp -> _bcq_host.so, the binding's host code."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbcq_hip.so")
+HOST_SOURCE = os.path.join(CSRC, "bcq_host.cpp")
+HOST_LIB = os.path.join(HERE, "_bcq_host.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -23,7 +26,9 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(HOST_LIB):
+        return True
+    if os.path.getmtime(HOST_SOURCE) > os.path.getmtime(HOST_LIB):
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
@@ -52,7 +57,23 @@ def build(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(link), flush=True)
         subprocess.run(link, check=True)
+    build_host(verbose)
     return LIB
+
+
+def build_host(verbose: bool = False) -> str:
+    """The binding's host code, against the torch that is installed (host compiler, no GPU code)."""
+    import torch
+    torch_dir = os.path.dirname(torch.__file__)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(torch_dir, "include"), "-isystem", "/opt/rocm/include",
+           "-isystem", sysconfig.get_paths()["include"], "-o", HOST_LIB, HOST_SOURCE,
+           "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return HOST_LIB
 
 
 if __name__ == "__main__":
