@@ -72,7 +72,7 @@ struct PlaneMfmaParams {
     uint32_t x_stride;                      // bytes between requests:    n * 2
     uint32_t m;
     int batch, p_max, uniform_p;
-    int KS, RB, nchunk, nslices;
+    int KS, RB, nslices;
     int glast;                              // 128-column groups in the last slice (8 unless n is not a multiple of 1024)
     // several matrices with the same n, p and activations in one launch (MULTI kernels): matrix k owns the
     // row blocks mat_blk0[k] .. mat_blk0[k+1]-1 of the grid; unused entries hold the total
@@ -240,7 +240,7 @@ __device__ __forceinline__ float sweep(const PlaneMfmaParams &pr, unsigned char 
 
     float acc = 0.f;
     int chunk = 0;
-    do {                                                            // nchunk >= 1
+    do {                                                            // (at least one chunk)
         const int slice = __builtin_amdgcn_readfirstlane(chunk * KS + ks);      // the same in all lanes of a wave
         const bool slice_ok = slice < pr.nslices;                   // the last chunk may be ragged
         const int p_eff = slice_ok ? p_mine : 0;
@@ -455,7 +455,7 @@ __device__ __forceinline__ float sweep(const PlaneMfmaParams &pr, unsigned char 
         }
         asm volatile("" : "+v"(acc));                               // the sums are due here, not past the branch below
         if (RB > 1) __syncthreads();                                // image no longer read: the next chunk may replace it
-    } while (++chunk < pr.nchunk);
+    } while (++chunk * KS < pr.nslices);
     return acc;
 }
 
@@ -464,8 +464,8 @@ __device__ __forceinline__ float sweep(const PlaneMfmaParams &pr, unsigned char 
 // So do groups of 64 columns (twice the scales and two results per plane in flight).
 __host__ __device__ constexpr int max_waves(int NB, bool mixed, int gs = 0) { return (NB == 4 && mixed) || gs < 0 ? 8 : 16; }
 
-template <int P, int NB, bool MIXED, bool OFFSET, bool MULTI = false, int GS = 0>
-__global__ __launch_bounds__(64 * max_waves(NB, MIXED, GS)) void plane_mfma_kernel(PlaneMfmaParams pr_in)
+template <int P, int NB, bool MIXED, bool OFFSET, bool MULTI, int GS>
+__device__ __forceinline__ void plane_mfma_body(const PlaneMfmaParams &pr_in, const uint32_t wg0 = 0)
 {
     PlaneMfmaParams pr = pr_in;               // MULTI kernels overwrite the per-matrix fields below
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -477,7 +477,7 @@ __global__ __launch_bounds__(64 * max_waves(NB, MIXED, GS)) void plane_mfma_kern
     // One request per tile (NB == 1): a workgroup is one row block, wave = K slice, the grid is exact.
     // Otherwise RB row blocks share a workgroup and the batch tiles of a row-block group are spread over ids.
     int RB = 1, ks = wave, rb = 0;            // K slice of this wave inside a chunk, row block inside the workgroup
-    uint32_t tile = 0, wg = blockIdx.x;
+    uint32_t tile = 0, wg = blockIdx.x - wg0;
     if constexpr (NB > 1) {
         // all of this without branches, so that every kernel argument is fetched in one go
         RB = pr.RB;
@@ -579,6 +579,64 @@ __global__ __launch_bounds__(64 * max_waves(NB, MIXED, GS)) void plane_mfma_kern
         for (int k = 0; k < KS; ++k) v += red[(rb * KS + k) * 64 + lane];
         if (row_ok && q < nb) pr.y[(size_t)(b0 + q) * pr.m + row] = (_Float16)v;
     }
+}
+
+template <int P, int NB, bool MIXED, bool OFFSET, bool MULTI = false, int GS = 0>
+__global__ __launch_bounds__(64 * max_waves(NB, MIXED, GS)) void plane_mfma_kernel(PlaneMfmaParams pr)
+{
+    plane_mfma_body<P, NB, MIXED, OFFSET, MULTI, GS>(pr);
+}
+
+// One request: what a wave needs before its first load as the first fourteen dwords of plain arguments, which the packet processor leaves in
+// scalar registers (kernel argument preloading, build.py) before the wave starts; read from memory, as a struct is, they cost
+// every wave of the launch a memory latency first.  1024 x 4096 at p = 2 2.90 -> 2.81 us, 14336 x 4096 at p = 4 9.25 -> 8.71, 5120 x 17920 at p = 3
+// with offsets 17.6 -> 17.0.  Everything else follows from the width; ks_row: bytes of a plane row, K slices of a chunk in the upper byte.
+__device__ __forceinline__ PlaneMfmaParams single_params(const unsigned char *planes, const unsigned char *x, _Float16 *y, uint32_t m,
+                                                         uint32_t ks_row, uint32_t scale_row_stride)
+{
+    PlaneMfmaParams pr{};
+    const uint32_t row_stride = ks_row & 0xffffffu;
+    pr.planes = planes;
+    pr.x = x;
+    pr.y = y;
+    pr.m = m;
+    pr.row_stride = row_stride;
+    pr.scale_row_stride = scale_row_stride;
+    pr.plane_stride = m * row_stride;
+    pr.scale_plane_stride = m * scale_row_stride;
+    pr.batch = 1;
+    pr.RB = 1;
+    pr.KS = (int)(ks_row >> 24);
+    pr.glast = (int)((row_stride / 16 - 1) % kSliceGroups) + 1;
+    pr.nslices = (int)((row_stride + kSliceCols / 8 - 1) / (kSliceCols / 8));
+    return pr;
+}
+
+template <int P, bool OFFSET, int GS>
+__global__ __launch_bounds__(64 * max_waves(1, false, GS)) void plane_mfma_single_kernel(const unsigned char *planes, const unsigned char *x,
+                                                                                         const unsigned char *scales, uint32_t m, uint32_t ks_row,
+                                                                                         uint32_t scale_row_stride, _Float16 *y,
+                                                                                         const unsigned char *offsets)
+{
+    PlaneMfmaParams pr = single_params(planes, x, y, m, ks_row, scale_row_stride);
+    pr.scales[P] = scales;
+    pr.offsets[P] = offsets;
+    plane_mfma_body<P, 1, false, OFFSET, false, GS>(pr);
+}
+
+// ... and two matrices in one launch: the row blocks of the second start at workgroup blk1 (two of 14336 x 4096 at
+// p = 4 / 3: 14.6 -> 14.2 / 12.2 -> 11.8 us).  Three matrices and more have more pointers than fit.
+template <int P>
+__global__ __launch_bounds__(64 * max_waves(1, false, 0)) void plane_mfma_pair_kernel(const unsigned char *x, const unsigned char *planes0,
+                                                                                      const unsigned char *planes1, const unsigned char *scales0,
+                                                                                      const unsigned char *scales1, uint32_t blk1, uint32_t m0, uint32_t m1,
+                                                                                      uint32_t ks_row, _Float16 *y0, _Float16 *y1)
+{
+    const bool second = blockIdx.x >= blk1;
+    const uint32_t scale_row_stride = (ks_row & 0xffffffu) / 8;         // groups of 128 columns
+    PlaneMfmaParams pr = single_params(second ? planes1 : planes0, x, second ? y1 : y0, second ? m1 : m0, ks_row, scale_row_stride);
+    pr.scales[P] = second ? scales1 : scales0;
+    plane_mfma_body<P, 1, false, false, false, 0>(pr, second ? blk1 : 0u);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -946,7 +1004,7 @@ int lds_total(int NB, int KS, int RB)
 }
 
 struct Plan {
-    int NB, KS, RB, nchunk;
+    int NB, KS, RB;
     size_t lds_bytes;
 };
 
@@ -963,7 +1021,6 @@ Plan make_plan(const GemmArgs &a, bool share_row_blocks = true)
         if (nslices % d == 0) KS = d;
     if (KS < ks_cap / 2 && nslices > ks_cap) KS = ks_cap;   // awkward factorisation: ragged last chunk instead
     pl.KS = KS;
-    pl.nchunk = (nslices + KS - 1) / KS;
     // With one request a workgroup is one row block: every wave builds its own slice of the operand image and no
     // wave waits for another before the final combine.  With more, 2 or 4 row blocks share a workgroup and its
     // image (each wave converts one request slot): that halves or quarters the conversion work of a tile, at the
@@ -990,9 +1047,39 @@ hipError_t launch_one(K kernel, const PlaneMfmaParams &pr, const Plan &pl, dim3 
     return hipGetLastError();
 }
 
+template <int P, bool OFFSET, int GS>
+hipError_t launch_single(const PlaneMfmaParams &pr, const Plan &pl, dim3 grid, dim3 block, hipStream_t stream)
+{
+    auto kernel = plane_mfma_single_kernel<P, OFFSET, GS>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), (int)pl.lds_bytes)) return e;
+    hipLaunchKernelGGL(kernel, grid, block, pl.lds_bytes, stream, pr.planes, pr.x, pr.scales[P], pr.m, pr.row_stride | (uint32_t)pr.KS << 24,
+                       pr.scale_row_stride, pr.y, pr.offsets[P]);
+    return hipGetLastError();
+}
+
+template <int P>
+hipError_t launch_pair(const PlaneMfmaParams &pr, const Plan &pl, dim3 grid, dim3 block, hipStream_t stream)
+{
+    auto kernel = plane_mfma_pair_kernel<P>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), (int)pl.lds_bytes)) return e;
+    hipLaunchKernelGGL(kernel, grid, block, pl.lds_bytes, stream, pr.x, pr.mat_planes[0], pr.mat_planes[1], pr.mat_scales[0], pr.mat_scales[1],
+                       pr.mat_blk0[1], pr.mat_m[0], pr.mat_m[1], pr.row_stride | (uint32_t)pr.KS << 24, pr.mat_y[0], pr.mat_y[1]);
+    return hipGetLastError();
+}
+
 template <int NB, bool OFFSET, int GS>
 hipError_t launch_group(const GemmArgs &a, const PlaneMfmaParams &pr, const Plan &pl, dim3 grid, dim3 block, hipStream_t stream)
 {
+    if constexpr (NB == 1) {
+        if (a.batch == 1 && a.uniform_p > 0) {
+            switch (a.uniform_p) {
+            case 1: return launch_single<1, OFFSET, GS>(pr, pl, grid, block, stream);
+            case 2: return launch_single<2, OFFSET, GS>(pr, pl, grid, block, stream);
+            case 3: return launch_single<3, OFFSET, GS>(pr, pl, grid, block, stream);
+            default: return launch_single<4, OFFSET, GS>(pr, pl, grid, block, stream);
+            }
+        }
+    }
     if (a.uniform_p == 0) return launch_one(plane_mfma_kernel<kMaxP, NB, true, OFFSET, false, GS>, pr, pl, grid, block, stream);
     switch (a.uniform_p) {
     case 1: return launch_one(plane_mfma_kernel<1, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
@@ -1220,7 +1307,6 @@ hipError_t plane_mfma_launch(const GemmArgs &a, hipStream_t stream)
     pr.uniform_p = a.uniform_p;
     pr.KS = pl.KS;
     pr.RB = pl.RB;
-    pr.nchunk = pl.nchunk;
     pr.nslices = (int)((a.n + kSliceCols - 1) / kSliceCols);
     pr.glast = (int)((a.n / 128 - 1) % kSliceGroups) + 1;
     const int64_t row_blocks = (a.m + 15) / 16;
@@ -1278,7 +1364,6 @@ hipError_t plane_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t 
     if (const StreamPlan sp = make_stream_plan_multi(mats, count); sp.ok) return launch_stream(mats, count, pr, sp, stream);
     pr.KS = pl.KS;
     pr.RB = 1;
-    pr.nchunk = pl.nchunk;
     pr.nslices = (int)((a.n + kSliceCols - 1) / kSliceCols);
     pr.glast = (int)((a.n / 128 - 1) % kSliceGroups) + 1;
     uint32_t blk = 0;
@@ -1297,6 +1382,14 @@ hipError_t plane_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t 
     pr.inv_span = 1.0f / (float)(8 * pr.ntiles);
     pr.inv_ks = 1.0f / (float)pl.KS;
     dim3 block(64 * pl.KS);
+    if (pl.NB == 1 && count == 2 && a.batch == 1) {
+        switch (a.uniform_p) {
+        case 1: return launch_pair<1>(pr, pl, grid, block, stream);
+        case 2: return launch_pair<2>(pr, pl, grid, block, stream);
+        case 3: return launch_pair<3>(pr, pl, grid, block, stream);
+        default: return launch_pair<4>(pr, pl, grid, block, stream);
+        }
+    }
     switch (pl.NB) {
     case 1: return launch_multi_nb<1>(a.uniform_p, pr, pl, grid, block, stream);
     case 2: return launch_multi_nb<2>(a.uniform_p, pr, pl, grid, block, stream);
