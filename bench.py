@@ -14,7 +14,7 @@ Prints ONE JSON line:
   value     effective HBM GB/s over the timed steps = algorithmic bytes / time,
             algorithmic bytes per call = m*n*p/8 (planes) + m*(n/128)*p*2
             (scales) + n*2 (x) + m*2 (y)
-  roofline  the dominant kernel (plane_mfma_kernel<4> on a 14336x4096 layer):
+  roofline  the dominant kernel (plane_mfma_single_kernel<4> on a 14336x4096 layer):
             algorithmic bytes per launch / mean launch duration, measured with
             HIP events around back-to-back launches on the launch stream,
             against the 8 TB/s HBM peak
@@ -70,7 +70,7 @@ def profiled_traffic_bytes(p, m, n):
     scaled by a plain copy).  The summary names the sha256 of the kernel source it was taken with; if the source has
     changed since, or the summary does not cover this kernel, the figure is None (never a stale number).
     Returns (bytes or None, note)."""
-    want = (f"plane_mfma_kernel<{p},1,false>", f"{m}x{n}")
+    want = (f"plane_mfma_single_kernel<{p},false,0>", f"{m}x{n}")
     try:
         text = open(TRAFFIC_PROFILE).read()
     except OSError:
@@ -465,7 +465,7 @@ def main():
     dom_bytes = syn.algorithmic_bytes(dm, dn, dom_p, 1)
     achieved = dom_bytes / (dom_us * 1e-6) / 1e9
     traffic, traffic_note = profiled_traffic_bytes(dom_p, dm, dn)
-    roofline = {"bound": "hbm", "kernel": f"plane_mfma_kernel<{dom_p}> m={dm} n={dn} batch=1",
+    roofline = {"bound": "hbm", "kernel": f"plane_mfma_single_kernel<{dom_p}> m={dm} n={dn} batch=1",
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic, "traffic_source": traffic_note,
                 "bytes_per_launch": dom_bytes, "us_per_launch": round(dom_us, 3)}
