@@ -31,9 +31,9 @@
 // weight is rebuilt once per precision and tile of requests by look-ups of that precision instead of by sums: 8192 x 8192 with 200
 // requests at precisions from {2, 3, 4} 119 -> 63 us (on 128 x 96: a third of 200 requests fills two tiles of 64 badly, one of 128 half).
 //
-// What bounds it: on a full chip the matrix instructions with the look-ups between them (matrix pipe busy for 63 / 55 / 47 % of the
-// cycles at p = 2 / 3 / 4) and the clock, which random operands hold at 1.7 to 1.95 GHz (with activations of zero the same cycles
-// pass at 2.3 to 2.4); the library's plain fp16 product of 8192^3 reaches 1210 TFLOP/s (1750 with zeros).  Smaller tiles were bound
+// What bounds it: on a full chip the matrix instructions with the look-ups between them (matrix pipe busy for 66 / 63 / 57 % of the
+// cycles at p = 2 / 3 / 4) and the clock, which random operands hold at 1.7 to 1.8 GHz (with activations of zero the same cycles
+// pass at 2.2 to 2.3); the library's plain fp16 product of 8192^3 reaches 1210 TFLOP/s (1750 with zeros).  Smaller tiles were bound
 // by neither: leaving out the look-ups, three quarters of the matrix instructions or the operand reads changed nothing, while leaving out the
 // fetch of words and scales took a quarter off (4096 x 14336 with 500 requests at p = 4 on tiles of 128 x 256: 240 -> 164 us), because
 // every row, plane and pair of groups asked for a line of its own, twice (see fetch_block and load_window).  That halved (196 us there):
