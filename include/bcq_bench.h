@@ -65,6 +65,14 @@ int bcq_select_dequant_shape(int request_tiles, int row_blocks);
  */
 int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks);
 
+/*
+ * What a workgroup of the level form keeps and asks for, for a product of n columns at precision p on shape (1, row_blocks):
+ * layout[0] bytes of LDS, [1] columns of a row whose scales are in LDS at a time, [2] loads that fetch those of all its rows, each
+ * of 256 bytes, [3] columns of plane words fetched at a time.  Needs no GPU.  Returns 0, -1 NULL, or -6 if the form does not take
+ * the problem.
+ */
+int bcq_level_layout(int p, int row_blocks, int64_t n, int group, int with_offsets, int *layout);
+
 /* Name of the variant the calling thread's most recent successful launch used ("" before any): "sign_select",
  * "lut", "plane_mfma" ("plane_mfma_rows" where that family ran in its row-streaming form: tall matrices with two to eight
  * requests, or with one request at one or two planes), "dequant_mfma", "plane_f16", "quantize". */

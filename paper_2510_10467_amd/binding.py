@@ -48,6 +48,8 @@ def lib() -> ctypes.CDLL:
         L.bcq_last_kernel.restype = ctypes.c_char_p
         L.bcq_dequant_shape_for.argtypes = [i32, i64, i64, i32, i32, i32, vp, vp]
         L.bcq_dequant_shape_for.restype = i32
+        L.bcq_level_layout.argtypes = [i32, i32, i64, i32, i32, vp]
+        L.bcq_level_layout.restype = i32
         L.bcq_pack.argtypes = [vp, vp, i32, i64, i64, vp]
         L.bcq_unpack.argtypes = [vp, vp, i32, i64, i64, vp]
         L.bcq_gemv.argtypes = [vp, vp, i32, vp, vp, i64, i64, i32, i32, vp]
@@ -112,6 +114,13 @@ def dequant_shape_for(p: int, m: int, n: int, batch: int, group: int = 128, with
     _check(lib().bcq_dequant_shape_for(p, m, n, batch, group, int(with_offsets), ctypes.byref(pair, 0), ctypes.byref(pair, 4)),
            "bcq_dequant_shape_for")
     return pair[0], pair[1]
+
+
+def level_layout(p: int, row_blocks: int, n: int, group: int = 128, with_offsets: bool = False) -> dict:
+    """Benchmarks and tests: what a workgroup of the level form keeps and asks for on shape ``(1, row_blocks)``."""
+    got = (ctypes.c_int * 4)()
+    _check(lib().bcq_level_layout(p, row_blocks, n, group, int(with_offsets), got), "bcq_level_layout")
+    return dict(zip(("lds_bytes", "window_columns", "window_loads", "word_columns"), got))
 
 
 def last_kernel() -> str:

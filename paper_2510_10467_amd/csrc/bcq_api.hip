@@ -98,6 +98,22 @@ int choose(const bcq::GemmArgs &a)
     return choice;
 }
 
+// A product of this size that the large-batch kernels take, for questions that need no tensors; false if they do not take it.
+bool sizes_only(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, bcq::GemmArgs &a)
+{
+    if (p < 1 || p > BCQ_MAX_PLANES || check_shape(m, n, batch, group) != BCQ_OK || batch < 1) return false;
+    static const _Float16 set{};        // (only whether there are offsets is asked)
+    a = {};
+    a.scales[p] = &set;
+    a.offsets[p] = with_offsets ? &set : nullptr;
+    a.uniform_p = a.p_max = p;
+    a.m = m;
+    a.n = n;
+    a.batch = batch;
+    a.group = group;
+    return bcq::dequant_mfma_supports(a);
+}
+
 int run(const bcq::GemmArgs &a, hipStream_t stream)
 {
     using namespace bcq;
@@ -191,18 +207,23 @@ int bcq_select_dequant_shape(int request_tiles, int row_blocks)
 int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks)
 {
     if (!request_tiles || !row_blocks) return BCQ_ERR_NULL;
-    if (p < 1 || p > BCQ_MAX_PLANES || check_shape(m, n, batch, group) != BCQ_OK || batch < 1) return BCQ_ERR_VARIANT;
-    static const _Float16 set{};        // (only whether there are offsets is asked)
-    bcq::GemmArgs a{};
-    a.scales[p] = &set;
-    a.offsets[p] = with_offsets ? &set : nullptr;
-    a.uniform_p = a.p_max = p;
-    a.m = m;
-    a.n = n;
-    a.batch = batch;
-    a.group = group;
-    if (!bcq::dequant_mfma_supports(a) || !bcq::dequant_mfma_shape_fits(a)) return BCQ_ERR_VARIANT;
+    bcq::GemmArgs a;
+    if (!sizes_only(p, m, n, batch, group, with_offsets, a) || !bcq::dequant_mfma_shape_fits(a)) return BCQ_ERR_VARIANT;
     bcq::dequant_mfma_shape(a, *request_tiles, *row_blocks);
+    return BCQ_OK;
+}
+
+int bcq_level_layout(int p, int row_blocks, int64_t n, int group, int with_offsets, int *layout)
+{
+    if (!layout) return BCQ_ERR_NULL;
+    bcq::GemmArgs a;
+    const int shape = row_blocks - 100;
+    if (shape < 0 || shape >= bcq::kLevelShapeCount || !sizes_only(p, 64, n, 1, group, with_offsets, a) || !bcq::level_mfma_supports(a)) return BCQ_ERR_VARIANT;
+    const bcq::LevelLayout l = bcq::level_mfma_layout(a, shape);
+    layout[0] = l.lds_bytes;
+    layout[1] = l.window_columns;
+    layout[2] = l.window_loads;
+    layout[3] = l.word_columns;
     return BCQ_OK;
 }
 

@@ -109,6 +109,11 @@ int level_mfma_cheapest(const GemmArgs &a, float &us);
 // Per-request precision: the same body per precision, each workgroup on the requests of one precision.  a: the call, with uniform_p the
 // deepest precision and batch the requests that a precision is expected to have; nsets: that many precisions.
 int level_mfma_cheapest_classes(const GemmArgs &a, int nsets, float &us);
+// What a workgroup keeps and asks for (bcq_level_layout)
+struct LevelLayout {
+    int lds_bytes, window_columns, window_loads, word_columns;
+};
+LevelLayout level_mfma_layout(const GemmArgs &a, int shape);
 hipError_t level_mfma_launch_classes(const GemmArgs &a, uint32_t class_order, int shape, hipStream_t stream);
 // The estimate of both large-batch forms: `at_4096` is what a product of 4096 columns takes, of which `start` does not depend
 // on the width (beyond 4096 columns it no longer counts).

@@ -224,12 +224,17 @@ struct Lds {
     static constexpr int WAVES = S::TEAMS * S::SW;
     static constexpr int HANDOVER = COALESCE ? 2048 : 0;            // per wave
     static constexpr int SCALES_AT = S::TILES + WAVES * HANDOVER;
-    static constexpr int PLANES = P + (OFFSET ? 1 : 0);             // offsets are kept like another plane's scales
-    static constexpr int limit = S::QT == 2 && S::WR == 4 ? 80 * 1024 : 160 * 1024;
+    // two workgroups share a CU
+    static constexpr bool PAIRED = S::QT == 2 && S::WR == 4;
+    static constexpr int limit = PAIRED ? 80 * 1024 : 160 * 1024;
+    // Offsets are kept like another plane's scales, except where a fifth plane would leave room for one workgroup on a CU instead of two: there
+    // every lane reads its own from memory (128 x 64, p = 4, groups of 128, 400 workgroups: 1024 columns 24.9 -> 20.8 us, 4096 72.1 -> 64.5).
+    static constexpr bool Z_DIRECT = OFFSET && PAIRED && SCALES_AT + S::ROWS * (P + 1) * 16 * S::TEAMS > limit;
+    static constexpr int PLANES = P + (OFFSET && !Z_DIRECT ? 1 : 0);
     // bytes of a row's scales of one plane in LDS; at least those of two rounds in groups of 64
     static constexpr int WINDOW = SCALES_AT + S::ROWS * PLANES * 64 <= limit ? 64 : SCALES_AT + S::ROWS * PLANES * 32 <= limit || S::TEAMS > 1 ? 32 : 16;
     static constexpr int BYTES = SCALES_AT + S::ROWS * PLANES * WINDOW;
-    static_assert(BYTES <= 160 * 1024, "must fit in LDS");
+    static_assert(BYTES <= limit, "must fit in LDS, twice where two workgroups share it");
     static_assert(WINDOW >= 16 * S::TEAMS, "a window holds the scales of two rounds in groups of 64");
 };
 
@@ -300,6 +305,8 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
     uint32_t sc[P], zc = 0;                 // scales and offset of the next pair: low half first, high half columns 64 .. (groups of 64)
 #pragma unroll
     for (int i = 0; i < P; ++i) sc[i] = 0;
+    uint32_t z_word = 0;
+    const uint32_t z_off = my_row * a.scale_row_stride + (a.gshift > 0 ? 0u : a.gshift < 0 ? half * 4u : half * 2u);
     uint32_t wq_off[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) wq_off[j] = min(row0 + 16 * j + (lane >> 2), a.m - 1) * a.row_stride;
@@ -316,11 +323,15 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
     const int last = a.npairs - 1;
     auto pair_of = [&](int it) { return (it >> 1) * (2 * TEAMS) + (it & 1) + (it == rounds - 1 && !(it & 1) ? team : 2 * team); };
 
+    const auto s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.scales), 0, (int)(((uint32_t)P * a.scale_plane_stride + 3) & ~3u), 0x00020000);
+    const auto z_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(OFFSET ? a.offsets : a.scales), 0, (int)((a.scale_plane_stride + 3) & ~3u), 0x00020000);
     auto fetch_direct = [&](int pair) {     // 16 bytes of the lane's own row
         asm volatile("" : "+v"(w_off));     // lane offsets stay 32 bits wide, in the load's own addressing mode
 #pragma unroll
         for (int i = 0; i < P; ++i)
             word_n[i][0] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + (uint32_t)pair * 32 + w_off);
+        // and the dword of the pair's offset
+        if constexpr (M::Z_DIRECT) z_word = __builtin_amdgcn_raw_buffer_load_b32(z_rsrc, (int)((z_off + (uint32_t)pair * s_pair) & ~3u), 0, 0);
     };
     auto fetch_block = [&](int pair) {      // the pair and its neighbour
         // (past the end of a row: its last part, for a pair that is not there)
@@ -338,8 +349,6 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
     // (Past the end of a row the next one follows, past the end of the set nothing is read; neither is used.)
     unsigned char *const scales_lds = lds + M::SCALES_AT;
     const uint32_t wg_row0 = rowblk * S::ROWS;
-    const auto s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.scales), 0, (int)(((uint32_t)P * a.scale_plane_stride + 3) & ~3u), 0x00020000);
-    const auto z_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(OFFSET ? a.offsets : a.scales), 0, (int)((a.scale_plane_stride + 3) & ~3u), 0x00020000);
     auto load_window = [&](int w) {
         constexpr int PER_ROW = WINDOW / 4, ROWS = 64 / PER_ROW;        // lanes per row, rows per load
         constexpr int PER_PLANE = S::ROWS / ROWS, LOADS = M::PLANES * PER_PLANE;
@@ -348,7 +357,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
 #pragma unroll 1
         for (int j = wave; j < LOADS; j += M::WAVES) {
             const int plane = j / PER_PLANE, row = j % PER_PLANE * ROWS + lane / PER_ROW;
-            const bool z = OFFSET && plane == P;
+            const bool z = OFFSET && !M::Z_DIRECT && plane == P;
             const uint32_t at = min(wg_row0 + row, a.m - 1) * a.scale_row_stride + col + (z ? 0u : (uint32_t)plane * a.scale_plane_stride);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(z ? z_rsrc : s_rsrc, (__attribute__((address_space(3))) void *)(scales_lds + j * 256), 4,
                                                      (int)((at & ~3u) + (lane % PER_ROW) * 4), 0, 0, 0);
@@ -367,6 +376,10 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
             else v = *reinterpret_cast<const unsigned short *>(from + ((sc_row + (i < P ? (uint32_t)i * a.scale_plane_stride : 0u)) & 2));
             if (i < P) sc[i < P ? i : 0] = v;
             else zc = v;
+        }
+        if constexpr (M::Z_DIRECT) {
+            const uint32_t at = z_off + (uint32_t)pair * s_pair;
+            zc = a.gshift < 0 ? z_word : (z_word >> (8 * (at & 2))) & 0xffffu;
         }
     };
 
@@ -456,7 +469,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
             return;
         }
         const int npair = min(pair_of(it + 1), last);               // (past the end: something that is there, for nothing)
-        constexpr int FETCHED = COALESCE ? (SECOND ? 0 : 2 * P) : P;        // loads of the words that come next
+        constexpr int FETCHED = COALESCE ? (SECOND ? 0 : 2 * P) : P + (M::Z_DIRECT ? 1 : 0);        // loads of the words that come next
         // the next pair opens a window: nobody needs the old one any more
         const int nstart = ((it + 1) >> 1) * (2 * TEAMS);
         if (SECOND && (nstart & (wpairs - 1)) == 0 && nstart <= last) load_window(nstart / wpairs);
@@ -633,6 +646,14 @@ hipError_t launch_byclass(const LevelParams &pr, hipStream_t stream)
     return hipGetLastError();
 }
 
+// what visit_shape hands its function: the kernel of a product
+template <int P_, typename S_, bool OFFSET_>
+struct Kernel {
+    static constexpr int P = P_;
+    using S = S_;
+    static constexpr bool OFFSET = OFFSET_;
+};
+
 template <int P, typename S, bool OFFSET>
 hipError_t launch(LevelParams pr, hipStream_t stream)
 {
@@ -653,14 +674,29 @@ hipError_t launch(LevelParams pr, hipStream_t stream)
     return hipGetLastError();
 }
 
-template <typename S>
-hipError_t launch_shape(const LevelParams &pr, int p, bool offset, hipStream_t stream)
+template <typename S, typename F>
+hipError_t visit(int p, bool offset, F f)
 {
     switch (p) {
-    case 1: return offset ? launch<1, S, true>(pr, stream) : launch<1, S, false>(pr, stream);
-    case 2: return offset ? launch<2, S, true>(pr, stream) : launch<2, S, false>(pr, stream);
-    case 3: return offset ? launch<3, S, true>(pr, stream) : launch<3, S, false>(pr, stream);
-    default: return offset ? launch<4, S, true>(pr, stream) : launch<4, S, false>(pr, stream);
+    case 1: return offset ? f(Kernel<1, S, true>{}) : f(Kernel<1, S, false>{});
+    case 2: return offset ? f(Kernel<2, S, true>{}) : f(Kernel<2, S, false>{});
+    case 3: return offset ? f(Kernel<3, S, true>{}) : f(Kernel<3, S, false>{});
+    default: return offset ? f(Kernel<4, S, true>{}) : f(Kernel<4, S, false>{});
+    }
+}
+
+// f(the kernel that a product at one precision runs with on a shape)
+template <typename F>
+hipError_t visit_shape(int shape, int p, bool offset, F f)
+{
+    switch (shape) {
+    case 0: return visit<Shape<8, 8, 1, 1>>(p, offset, f);
+    case 1: return visit<Shape<4, 4, 2, 1>>(p, offset, f);
+    case 2: return visit<Shape<4, 4, 1, 2>>(p, offset, f);
+    case 3: return visit<Shape<4, 2, 1, 2>>(p, offset, f);
+    case 4: return visit<Shape<2, 4, 1, 2>>(p, offset, f);
+    case 5: return visit<Shape<2, 2, 1, 4>>(p, offset, f);
+    default: return hipErrorInvalidValue;
     }
 }
 
@@ -672,7 +708,7 @@ hipError_t launch_shape(const LevelParams &pr, int p, bool offset, hipStream_t s
 // become about a tenth faster since.  start_us is the part of a round that does not shrink with the width: the
 // first three stages of activations have to arrive, the results to leave, the launch itself (4096 x 256 with 500 requests at
 // p = 4 on 128 x 128: 8.5 us, where an eighth of the columns' share of 4096 x 4096 would be 3).
-// The LDS of the tiles of 128 x 64 (64 KiB, and at most 116 registers) lets two of those workgroups share a CU, that of the others
+// The LDS of 128 x 64 (72 to 80 KiB, and at most 126 registers) lets two of those workgroups share a CU, that of the others
 // one.  Large tiles rebuild a weight for more requests, small ones keep the CUs busy on short matrices and batches.
 struct LevelShape {
     int rows, reqs;
@@ -806,15 +842,22 @@ hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, c
             pr.mat_m[k] = (uint32_t)mats[k].m;
         }
     }
-    switch (shape) {
-    case 0: return launch_shape<Shape<8, 8, 1, 1>>(pr, a.uniform_p, offset, stream);
-    case 1: return launch_shape<Shape<4, 4, 2, 1>>(pr, a.uniform_p, offset, stream);
-    case 2: return launch_shape<Shape<4, 4, 1, 2>>(pr, a.uniform_p, offset, stream);
-    case 3: return launch_shape<Shape<4, 2, 1, 2>>(pr, a.uniform_p, offset, stream);
-    case 4: return launch_shape<Shape<2, 4, 1, 2>>(pr, a.uniform_p, offset, stream);
-    case 5: return launch_shape<Shape<2, 2, 1, 4>>(pr, a.uniform_p, offset, stream);
-    default: return hipErrorInvalidValue;
-    }
+    return visit_shape(shape, a.uniform_p, offset, [&](auto k) {
+        using K = decltype(k);
+        return launch<K::P, typename K::S, K::OFFSET>(pr, stream);
+    });
+}
+
+LevelLayout level_mfma_layout(const GemmArgs &a, int shape)
+{
+    const LevelParams pr = level_params(a);
+    LevelLayout out{};
+    (void)visit_shape(shape, a.uniform_p, a.offsets[a.uniform_p] != nullptr, [&](auto k) {
+        using M = Lds<decltype(k)::P, typename decltype(k)::S, decltype(k)::OFFSET>;
+        out = {M::BYTES, 256 * (M::WINDOW / (pr.gshift > 0 ? 4 : pr.gshift < 0 ? 8 : 4)), decltype(k)::S::ROWS * M::PLANES * M::WINDOW / 256, M::COALESCE ? 512 : 256};
+        return hipSuccess;
+    });
+    return out;
 }
 
 }  // namespace bcq

@@ -6,6 +6,7 @@ import subprocess
 
 import pytest
 
+import paper_2510_10467_amd as bcq
 from paper_2510_10467_amd import build as hip_build
 
 LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
@@ -40,3 +41,17 @@ def test_two_waves_of_every_quantiser_share_a_simd(kernels):
     for name, (registers, scratch) in quantisers.items():
         assert registers <= 256, f"{name}: {registers} vector registers"
         assert scratch == 0, f"{name}: {scratch} bytes of scratch"
+
+
+def test_two_workgroups_of_the_128_x_64_tiles_share_a_cu(kernels):
+    """The level form's price of these tiles beyond 256 workgroups counts on two of them per CU: 160 KiB of LDS and, of eight waves each, 128
+    vector registers (128 x 64, p = 4 with offsets, 400 workgroups: 1024 columns 20.8 us with two per CU, 24.9 with one)."""
+    tiles = {name: use for name, use in kernels.items() if "level_mfma_kernel" in name and "5ShapeILi2ELi4E" in name}
+    assert len(tiles) == 8                                      # one to four planes with and without offsets
+    for name, (registers, scratch) in tiles.items():
+        assert registers <= 128 and scratch == 0, f"{name}: {registers} vector registers, {scratch} bytes of scratch"
+    for p in (1, 2, 3, 4):
+        for offsets in (False, True):
+            for group in (64, 128, 256):
+                used = bcq.level_layout(p, 104, 4096, group, offsets)["lds_bytes"]
+                assert 2 * used <= 160 * 1024, f"p={p} offsets={offsets} group={group}: {used} bytes of LDS"
