@@ -238,6 +238,22 @@ struct Lds {
     static_assert(WINDOW >= 16 * S::TEAMS, "a window holds the scales of two rounds in groups of 64");
 };
 
+// A window of scales in LDS: every row has 2^row_log2 bytes in a plane's part of it, the scales of `pairs` pairs of groups (a power of two).
+struct ScaleWindow {
+    int row_log2, pairs;
+};
+
+// window: Lds::WINDOW.  Rows start at multiples of two bytes (groups of 256 columns) or four; loads of four bytes fetch them from the multiple of four
+// below, and in groups of 256 a window is half of what it could be, so that nothing is cut off.  On narrow matrices a row's place holds
+// just the row, so that a load brings more of them: a workgroup starts with these loads (200 workgroups of 64 x 128, 256 columns, p = 4 with
+// offsets: 80 loads 9.4 us, 5 loads 8.4).
+__host__ __device__ inline ScaleWindow scale_window(int window, uint32_t scale_row_stride, int gshift, int npairs)
+{
+    const uint32_t row_bytes = scale_row_stride + (gshift > 0 && (npairs & 1) ? 2u : 0u);       // and what lies before an odd start
+    const int row_log2 = 32 - __builtin_clz((row_bytes < (uint32_t)window ? row_bytes : (uint32_t)window) - 1);
+    return {row_log2, window / (gshift < 0 ? 8 : 4)};
+}
+
 // the workgroup's rows (block rowblk of the matrix) and requests b0 .. b0 + nreq - 1
 // BYCLASS (per-request precision): the requests of precision P of rank b0 .. b0 + S::REQS - 1 among them instead; every wave ranks the batch
 // itself, the numbers pass through LDS before the tiles need it and wait in registers until the results are stored.
@@ -318,7 +334,6 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
 
     // The teams take blocks of two neighbouring pairs in turn; what is left after whole rounds of blocks goes out as single pairs if there are
     // no more of them than teams.
-    const int wpairs = WINDOW / (a.gshift > 0 ? 4 : (int)s_pair);       // pairs of a window
     const int rounds = (a.npairs + TEAMS - 1) / TEAMS;
     const int last = a.npairs - 1;
     auto pair_of = [&](int it) { return (it >> 1) * (2 * TEAMS) + (it & 1) + (it == rounds - 1 && !(it & 1) ? team : 2 * team); };
@@ -344,26 +359,29 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
             for (int i = 0; i < P; ++i) word_n[i][COALESCE ? j : 0] = *reinterpret_cast<const u32x4 *>(a.planes + (size_t)i * a.plane_stride + off);
         }
     };
-    // Window w of the scales of all the workgroup's rows, four bytes per lane.  Rows start at multiples of two bytes (groups of 256 columns) or
-    // four: a window begins at the multiple of four below, and in groups of 256 it is half of what it could be, so that nothing is cut off.
-    // (Past the end of a row the next one follows, past the end of the set nothing is read; neither is used.)
+    // Window w of the scales of all the workgroup's rows, four bytes per lane.  (Past the end of a row the next one follows; past the end of the set
+    // at most the two bytes that fill its last dword are read.  None of it is used.)
     unsigned char *const scales_lds = lds + M::SCALES_AT;
     const uint32_t wg_row0 = rowblk * S::ROWS;
+    const ScaleWindow sw = scale_window(WINDOW, a.scale_row_stride, a.gshift, a.npairs);
+    const int wpairs = sw.pairs;
     auto load_window = [&](int w) {
-        constexpr int PER_ROW = WINDOW / 4, ROWS = 64 / PER_ROW;        // lanes per row, rows per load
-        constexpr int PER_PLANE = S::ROWS / ROWS, LOADS = M::PLANES * PER_PLANE;
-        static_assert(S::ROWS % ROWS == 0, "a load covers rows of one plane");
+        constexpr int kRowsLog2 = __builtin_ctz(S::ROWS);
+        static_assert(S::ROWS == 1 << kRowsLog2 && S::ROWS >= 64, "a load covers rows of one plane");
+        const int per_row = sw.row_log2 - 2, per_plane = kRowsLog2 + sw.row_log2 - 8;       // lanes of a row, loads of a plane: their logarithms
         const uint32_t col = (uint32_t)(w * wpairs) * s_pair;
 #pragma unroll 1
-        for (int j = wave; j < LOADS; j += M::WAVES) {
-            const int plane = j / PER_PLANE, row = j % PER_PLANE * ROWS + lane / PER_ROW;
+        for (int j = wave; j < M::PLANES << per_plane; j += M::WAVES) {
+            const int plane = j >> per_plane, part = j & ((1 << per_plane) - 1);
+            const uint32_t row = (part << (6 - per_row)) + (lane >> per_row);
             const bool z = OFFSET && !M::Z_DIRECT && plane == P;
             const uint32_t at = min(wg_row0 + row, a.m - 1) * a.scale_row_stride + col + (z ? 0u : (uint32_t)plane * a.scale_plane_stride);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(z ? z_rsrc : s_rsrc, (__attribute__((address_space(3))) void *)(scales_lds + j * 256), 4,
-                                                     (int)((at & ~3u) + (lane % PER_ROW) * 4), 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(z ? z_rsrc : s_rsrc,
+                                                     (__attribute__((address_space(3))) void *)(scales_lds + plane * (S::ROWS * WINDOW) + part * 256), 4,
+                                                     (int)((at & ~3u) + (lane & ((1 << per_row) - 1)) * 4), 0, 0, 0);
         }
     };
-    const unsigned char *sc_lane = scales_lds + (row0 - wg_row0 + r32) * WINDOW + (a.gshift > 0 ? 0 : a.gshift < 0 ? half * 4 : half * 2);
+    const unsigned char *sc_lane = scales_lds + ((row0 - wg_row0 + r32) << sw.row_log2) + (a.gshift > 0 ? 0 : a.gshift < 0 ? half * 4 : half * 2);
     const uint32_t sc_row = my_row * a.scale_row_stride;
     auto read_scales = [&](int pair) {      // of a pair in the window that is there
         const unsigned char *at = sc_lane + (pair & (wpairs - 1)) * (int)s_pair;
@@ -854,7 +872,8 @@ LevelLayout level_mfma_layout(const GemmArgs &a, int shape)
     LevelLayout out{};
     (void)visit_shape(shape, a.uniform_p, a.offsets[a.uniform_p] != nullptr, [&](auto k) {
         using M = Lds<decltype(k)::P, typename decltype(k)::S, decltype(k)::OFFSET>;
-        out = {M::BYTES, 256 * (M::WINDOW / (pr.gshift > 0 ? 4 : pr.gshift < 0 ? 8 : 4)), decltype(k)::S::ROWS * M::PLANES * M::WINDOW / 256, M::COALESCE ? 512 : 256};
+        const ScaleWindow w = scale_window(M::WINDOW, pr.scale_row_stride, pr.gshift, pr.npairs);
+        out = {M::BYTES, 256 * w.pairs, M::PLANES * (decltype(k)::S::ROWS << w.row_log2) / 256, M::COALESCE ? 512 : 256};
         return hipSuccess;
     });
     return out;

@@ -100,3 +100,24 @@ def test_a_refused_shape_changes_nothing(knobs):
             assert bcq.dequant_shape_for(4, 28672, 8192, 500) == forced
     bcq.select_dequant_shape(0, 0)
     assert bcq.dequant_shape_for(4, 28672, 8192, 500) not in ((1, 103), (4, 8), (32, 2))
+
+
+# (row blocks of the shape, group, n): loads a plane of scales takes before the first weight, each of 256 bytes
+@pytest.mark.parametrize("blocks,group,n,loads", [
+    (104, 128, 256, 2), (104, 64, 256, 4), (104, 256, 256, 2), (104, 128, 512, 4), (104, 256, 768, 4), (104, 128, 1024, 8),
+    (103, 128, 256, 1), (103, 256, 256, 1), (103, 64, 512, 4), (101, 128, 256, 2), (100, 256, 512, 4)])
+def test_a_window_of_scales_is_no_wider_than_the_matrix(blocks, group, n, loads):
+    """A row of 256 columns in groups of 128 has four bytes of scales per plane: 64 rows in one load, not four (64 x 128, p = 4 with
+    offsets: 9.4 us with 80 loads ahead of the first weight, 8.4 with five)."""
+    for p in (1, 2, 3, 4):
+        assert bcq.level_layout(p, blocks, n, group, False)["window_loads"] == p * loads
+        if blocks != 104:                                       # (where every lane reads its own offset at p = 4)
+            assert bcq.level_layout(p, blocks, n, group, True)["window_loads"] == (p + 1) * loads
+
+
+def test_layout_refuses_what_the_form_does_not_take():
+    for bad in ((5, 104, 512), (0, 104, 512), (4, 99, 512), (4, 106, 512), (4, 104, 384), (4, 104, 512, 32), (4, 104, 512, 512)):
+        with pytest.raises(bcq.BcqError) as error:
+            bcq.level_layout(*bad)
+        assert error.value.status == -6
+    assert bcq.lib().bcq_level_layout(4, 104, 512, 128, 0, None) == -1

@@ -85,6 +85,27 @@ def test_every_weight_over_several_windows_of_scales(gpu, force, n, group, with_
             assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
 
 
+@pytest.mark.parametrize("n,group", [(256, 64), (256, 128), (512, 256), (768, 64), (1792, 256)])
+@pytest.mark.parametrize("with_offsets", [False, True])
+def test_every_weight_on_narrow_matrices(gpu, force, n, group, with_offsets):
+    """Rows whose scales take less than a window: 4, 8, 16 (an odd start, 14 bytes) and 32 bytes of LDS per row and plane; 131 rows, so that a
+    plane of scales starts at an odd multiple of two bytes in groups of 256, and a workgroup's last rows are not there."""
+    import paper_2510_10467_amd as bcq
+    m = 131
+    layer = syn.make_layer(m, n, group=group, seed=(958, n, group), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = gpu.to_dev(np.eye(n, dtype=np.float16))
+    for p in (1, 2, 3, 4):
+        z = syn.make_offsets(p, m, n, group, seed=(959, n, p)) if with_offsets else None
+        z_dev = None if z is None else gpu.to_dev(z)
+        expected = (weights16(layer, p, group, z).T + np.float16(0)).view(np.uint16)
+        for shape in SHAPES[:6]:
+            force(shape)
+            y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x, group=group, offsets=z_dev)
+            wrong = np.argwhere((y + 0.0).cpu().numpy().view(np.uint16) != expected)
+            assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
+
+
 @pytest.mark.parametrize("shape", SHAPES)
 def test_products_that_are_exact(gpu, force, shape):
     """Scales of 1, 1/4, 1/16, 1/64 and whole activations up to 8: every partial sum is a multiple of 1/64 below 2^14 and therefore
