@@ -244,14 +244,16 @@ struct ScaleWindow {
 };
 
 // window: Lds::WINDOW.  Rows start at multiples of two bytes (groups of 256 columns) or four; loads of four bytes fetch them from the multiple of four
-// below, and in groups of 256 a window is half of what it could be, so that nothing is cut off.  On narrow matrices a row's place holds
+// below, and a window is half of what it could be where that would cut something off: where rows or planes of scales start at odd multiples of two
+// and a row does not fit as a whole (half everywhere in groups of 256: 64 x 128, 6912 columns, p = 3 41.3 us, so 40.8).  On narrow matrices a row's place holds
 // just the row, so that a load brings more of them: a workgroup starts with these loads (200 workgroups of 64 x 128, 256 columns, p = 4 with
 // offsets: 80 loads 9.4 us, 5 loads 8.4).
 __host__ __device__ inline ScaleWindow scale_window(int window, uint32_t scale_row_stride, int gshift, int npairs)
 {
     const uint32_t row_bytes = scale_row_stride + (gshift > 0 && (npairs & 1) ? 2u : 0u);       // and what lies before an odd start
     const int row_log2 = 32 - __builtin_clz((row_bytes < (uint32_t)window ? row_bytes : (uint32_t)window) - 1);
-    return {row_log2, window / (gshift < 0 ? 8 : 4)};
+    const bool cut = gshift > 0 && (npairs & 1) && row_bytes > (uint32_t)window;
+    return {row_log2, window / (gshift < 0 ? 8 : gshift == 0 || cut ? 4 : 2)};
 }
 
 // the workgroup's rows (block rowblk of the matrix) and requests b0 .. b0 + nreq - 1

@@ -115,6 +115,19 @@ def test_a_window_of_scales_is_no_wider_than_the_matrix(blocks, group, n, loads)
             assert bcq.level_layout(p, blocks, n, group, True)["window_loads"] == (p + 1) * loads
 
 
+def test_windows_in_groups_of_256_are_whole_where_nothing_is_cut_off():
+    """A scale is two bytes; rows of an odd number of them start at odd multiples of two bytes every other time, between dwords."""
+    for p in (1, 2, 3, 4):
+        for offsets in (False, True):
+            window = 2 * bcq.level_layout(p, 103, 28672, 64, offsets)["window_columns"] // 64       # bytes of a row: two per group
+            whole = 256 * (window // 2)
+            columns = lambda n: bcq.level_layout(p, 103, n, 256, offsets)["window_columns"]
+            assert columns(28672) == whole                      # 112 groups: every row starts at a multiple of four bytes
+            assert columns(28672 - 256) == whole // 2           # 111
+            assert columns(whole - 256) == whole                # one group less than a window has place for: the row fits with what lies before it
+            assert columns(whole + 256) == whole // 2
+
+
 def test_layout_refuses_what_the_form_does_not_take():
     for bad in ((5, 104, 512), (0, 104, 512), (4, 99, 512), (4, 106, 512), (4, 104, 384), (4, 104, 512, 32), (4, 104, 512, 512)):
         with pytest.raises(bcq.BcqError) as error:
