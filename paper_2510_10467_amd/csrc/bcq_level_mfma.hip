@@ -202,10 +202,12 @@ __device__ __forceinline__ void transpose_codes(const uint32_t (&w)[P], uint32_t
     out[3] = __builtin_amdgcn_perm(q23, q01, 0x07060302u);
 }
 
-// QT tiles of 32 requests per wave (and one of 32 rows), WR x WQ waves per team
-template <int QT_, int WR_, int WQ_, int TEAMS_>
+// QT tiles of 32 requests per wave (and one of 32 rows), WR x WQ waves per team.  BLOCKS_FROM: from so many planes on plane words come for two
+// pairs of groups at a time (see fetch_block), kNever: for one.
+constexpr int kNever = kMaxP + 1;
+template <int QT_, int WR_, int WQ_, int TEAMS_, int BLOCKS_FROM_>
 struct Shape {
-    static constexpr int QT = QT_, WR = WR_, WQ = WQ_, TEAMS = TEAMS_;
+    static constexpr int QT = QT_, WR = WR_, WQ = WQ_, TEAMS = TEAMS_, BLOCKS_FROM = BLOCKS_FROM_;
     static constexpr int ROWS = 32 * WR, REQS = 32 * QT * WQ;
     static constexpr int SW = WR * WQ;                              // waves of a team
     static constexpr int THREADS = 64 * SW * TEAMS;
@@ -219,8 +221,7 @@ struct Shape {
 // LDS of a kernel: the tiles, then what it takes for plane words to change lanes, then the scales of a window of columns.
 template <int P, typename S, bool OFFSET>
 struct Lds {
-    // (not with 256 requests, where the registers are needed, nor where two workgroups share a CU, nor where it leaves no room for the scales)
-    static constexpr bool COALESCE = S::QT < 8 && !(S::QT == 2 && S::WR == 4) && !(OFFSET && P == 4);
+    static constexpr bool COALESCE = P >= S::BLOCKS_FROM && !(OFFSET && P == 4);        // (there it would leave no room for the scales)
     static constexpr int WAVES = S::TEAMS * S::SW;
     static constexpr int HANDOVER = COALESCE ? 2048 : 0;            // per wave
     static constexpr int SCALES_AT = S::TILES + WAVES * HANDOVER;
@@ -315,7 +316,7 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
     //                14336 with 500 requests: 240 us with, 192 without the fetch of every pair's scales)
     //   plane words  come for two pairs at a time, four neighbouring lanes on 64 bytes of a row (lane l: rows l / 4 and 16 + l / 4,
     //                part l % 4), which the memory pipe takes as one request, and change lanes in LDS (COALESCE: another 10 %, of
-    //                which the LDS takes 4 back)
+    //                which the LDS takes 4 back), where it pays (see visit_shape)
     using M = Lds<P, S, OFFSET>;
     constexpr bool COALESCE = M::COALESCE;
     constexpr int WINDOW = M::WINDOW;
@@ -334,11 +335,13 @@ __device__ __forceinline__ void level_body(const LevelParams &a, const int b0, i
     const unsigned char *get_at = handover + r32 * 64;
     const int get_swz = (r32 >> 2) & 3;
 
-    // The teams take blocks of two neighbouring pairs in turn; what is left after whole rounds of blocks goes out as single pairs if there are
-    // no more of them than teams.
     const int rounds = (a.npairs + TEAMS - 1) / TEAMS;
     const int last = a.npairs - 1;
-    auto pair_of = [&](int it) { return (it >> 1) * (2 * TEAMS) + (it & 1) + (it == rounds - 1 && !(it & 1) ? team : 2 * team); };
+    // The teams take pairs in turn, or with COALESCE blocks of two neighbouring ones, of which what is left after whole rounds of blocks goes out as
+    // single pairs if there are no more of them than teams.
+    auto pair_of = [&](int it) {
+        return COALESCE ? (it >> 1) * (2 * TEAMS) + (it & 1) + (it == rounds - 1 && !(it & 1) ? team : 2 * team) : it * TEAMS + team;
+    };
 
     const auto s_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(a.scales), 0, (int)(((uint32_t)P * a.scale_plane_stride + 3) & ~3u), 0x00020000);
     const auto z_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<unsigned char *>(OFFSET ? a.offsets : a.scales), 0, (int)((a.scale_plane_stride + 3) & ~3u), 0x00020000);
@@ -705,17 +708,31 @@ hipError_t visit(int p, bool offset, F f)
     }
 }
 
-// f(the kernel that a product at one precision runs with on a shape)
+// f(the kernel that a product at one precision runs with on a shape).  Words for two pairs of groups at a time against one (200 workgroups, 1536 /
+// 3840 / 14336 columns in groups of 128, microseconds):
+//   128 x 128, p = 4   21.8 / 43.8 / 132    against  21.8 / 44.2 / 137: from three planes on
+//              p = 2   17.1 / 34.7 / 108    against  16.6 / 34.0 / 108: not at one and two
+//   64 x 128,  p = 4   14.9 / 27.9 / 83.0   against  14.1 / 27.6 / 83.4: never
+//   64 x 64,   p = 4   11.1 / 19.8 / 56.9   against  10.3 / 19.4 / 57.2: not at three and four
+//              p = 2   9.2 / 15.2 / 41.6    against  8.6 / 14.2 / 45: at one and two beyond 5120 columns
+// A workgroup starts with both pairs of its first block, and of five pairs two teams get two and one team one.
+// (256 x 256 has no registers for it, 128 x 64 no LDS with two workgroups on a CU.)
 template <typename F>
-hipError_t visit_shape(int shape, int p, bool offset, F f)
+hipError_t visit_shape(int shape, int p, bool offset, int64_t n, F f)
 {
     switch (shape) {
-    case 0: return visit<Shape<8, 8, 1, 1>>(p, offset, f);
-    case 1: return visit<Shape<4, 4, 2, 1>>(p, offset, f);
-    case 2: return visit<Shape<4, 4, 1, 2>>(p, offset, f);
-    case 3: return visit<Shape<4, 2, 1, 2>>(p, offset, f);
-    case 4: return visit<Shape<2, 4, 1, 2>>(p, offset, f);
-    case 5: return visit<Shape<2, 2, 1, 4>>(p, offset, f);
+    case 0: return visit<Shape<8, 8, 1, 1, kNever>>(p, offset, f);
+    case 1: return visit<Shape<4, 4, 2, 1, 3>>(p, offset, f);
+    case 2: return visit<Shape<4, 4, 1, 2, 3>>(p, offset, f);
+    case 3: return visit<Shape<4, 2, 1, 2, kNever>>(p, offset, f);
+    case 4: return visit<Shape<2, 4, 1, 2, kNever>>(p, offset, f);
+    case 5:
+        if (p <= 2 && n > 5120) {
+            using Wide = Shape<2, 2, 1, 4, 1>;
+            if (p == 1) return offset ? f(Kernel<1, Wide, true>{}) : f(Kernel<1, Wide, false>{});
+            return offset ? f(Kernel<2, Wide, true>{}) : f(Kernel<2, Wide, false>{});
+        }
+        return visit<Shape<2, 2, 1, 4, kNever>>(p, offset, f);
     default: return hipErrorInvalidValue;
     }
 }
@@ -837,12 +854,12 @@ hipError_t level_mfma_launch_classes(const GemmArgs &a, uint32_t class_order, in
     pr.p_max = a.p_max;
     pr.class_order = class_order;
     switch (shape) {
-    case 1: return launch_byclass<Shape<4, 4, 2, 1>>(pr, stream);
-    case 2: return launch_byclass<Shape<4, 4, 1, 2>>(pr, stream);
-    case 3: return launch_byclass<Shape<4, 2, 1, 2>>(pr, stream);
-    case 4: return launch_byclass<Shape<2, 4, 1, 2>>(pr, stream);
-    case 5: return launch_byclass<Shape<2, 2, 1, 4>>(pr, stream);
-    case 6: return launch_byclass<Shape<3, 4, 1, 2>>(pr, stream);
+    case 1: return launch_byclass<Shape<4, 4, 2, 1, 3>>(pr, stream);
+    case 2: return launch_byclass<Shape<4, 4, 1, 2, 3>>(pr, stream);
+    case 3: return launch_byclass<Shape<4, 2, 1, 2, kNever>>(pr, stream);
+    case 4: return launch_byclass<Shape<2, 4, 1, 2, kNever>>(pr, stream);
+    case 5: return launch_byclass<Shape<2, 2, 1, 4, kNever>>(pr, stream);
+    case 6: return launch_byclass<Shape<3, 4, 1, 2, 3>>(pr, stream);
     default: return hipErrorInvalidValue;
     }
 }
@@ -862,7 +879,7 @@ hipError_t level_mfma_launch(const GemmArgs &a, int shape, hipStream_t stream, c
             pr.mat_m[k] = (uint32_t)mats[k].m;
         }
     }
-    return visit_shape(shape, a.uniform_p, offset, [&](auto k) {
+    return visit_shape(shape, a.uniform_p, offset, a.n, [&](auto k) {
         using K = decltype(k);
         return launch<K::P, typename K::S, K::OFFSET>(pr, stream);
     });
@@ -872,7 +889,7 @@ LevelLayout level_mfma_layout(const GemmArgs &a, int shape)
 {
     const LevelParams pr = level_params(a);
     LevelLayout out{};
-    (void)visit_shape(shape, a.uniform_p, a.offsets[a.uniform_p] != nullptr, [&](auto k) {
+    (void)visit_shape(shape, a.uniform_p, a.offsets[a.uniform_p] != nullptr, a.n, [&](auto k) {
         using M = Lds<decltype(k)::P, typename decltype(k)::S, decltype(k)::OFFSET>;
         const ScaleWindow w = scale_window(M::WINDOW, pr.scale_row_stride, pr.gshift, pr.npairs);
         out = {M::BYTES, 256 * w.pairs, M::PLANES * (decltype(k)::S::ROWS << w.row_log2) / 256, M::COALESCE ? 512 : 256};

@@ -128,6 +128,17 @@ def test_windows_in_groups_of_256_are_whole_where_nothing_is_cut_off():
             assert columns(whole + 256) == whole // 2
 
 
+def test_words_for_two_pairs_of_groups_at_a_time_only_where_that_is_ahead():
+    columns = lambda p, blocks, n, offsets=False: bcq.level_layout(p, blocks, n, 128, offsets)["word_columns"]
+    for n in (1536, 5120, 14336):
+        for blocks in (101, 102):
+            assert [columns(p, blocks, n) for p in (1, 2, 3, 4)] == [256, 256, 512, 512] and columns(4, blocks, n, True) == 256
+        for blocks in (100, 103, 104):
+            assert {columns(p, blocks, n) for p in (1, 2, 3, 4)} == {256}
+        assert {columns(p, 105, n) for p in (3, 4)} == {256}
+        assert {columns(p, 105, n) for p in (1, 2)} == {512 if n > 5120 else 256}
+
+
 def test_layout_refuses_what_the_form_does_not_take():
     for bad in ((5, 104, 512), (0, 104, 512), (4, 99, 512), (4, 106, 512), (4, 104, 384), (4, 104, 512, 32), (4, 104, 512, 512)):
         with pytest.raises(bcq.BcqError) as error:
