@@ -53,7 +53,7 @@ int bcq_selected_kernel(void);
  * precision uses the row blocks and whether the tile has 32 requests only, beyond 64 requests the whole shape if it
  * has 64 requests or more.  (1, 100) .. (1, 105) force the level form (rows rebuilt by look-ups, n a multiple of 256,
  * all but the first also for per-request precision from 33 requests on, per precision) with 256 x 256, 128 x 256, 128 x 128, 64 x 128, 128 x 64
- * and 64 x 64 rows x requests.  (0, 0) restores the automatic choice.  Returns 0, or -6 for any other pair.
+ * and 64 x 64 rows x requests, (1, 96) with 128 x 96, for per-request precision only.  (0, 0) restores the automatic choice.  Returns 0, or -6 for any other pair.
  */
 int bcq_select_dequant_shape(int request_tiles, int row_blocks);
 
@@ -64,6 +64,13 @@ int bcq_select_dequant_shape(int request_tiles, int row_blocks);
  * the problem.
  */
 int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks);
+
+/*
+ * Per-request precision: the shape of the level form that BCQ_KERNEL_DEQUANT_MFMA runs a call with, as a pair of
+ * bcq_select_dequant_shape, or (0, 0) where its other kernels run it.  precisions: bit q set where there is a scale set of precision
+ * q (1 .. 4).  Needs no GPU.  Returns 0, -1 NULL, or -6 if that kernel does not take the problem.
+ */
+int bcq_mixed_shape_for(int precisions, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks);
 
 /*
  * What a workgroup of the level form keeps and asks for, for a product of n columns at precision p on shape (1, row_blocks):

@@ -48,6 +48,8 @@ def lib() -> ctypes.CDLL:
         L.bcq_last_kernel.restype = ctypes.c_char_p
         L.bcq_dequant_shape_for.argtypes = [i32, i64, i64, i32, i32, i32, vp, vp]
         L.bcq_dequant_shape_for.restype = i32
+        L.bcq_mixed_shape_for.argtypes = [i32, i64, i64, i32, i32, i32, vp, vp]
+        L.bcq_mixed_shape_for.restype = i32
         L.bcq_level_layout.argtypes = [i32, i32, i64, i32, i32, vp]
         L.bcq_level_layout.restype = i32
         L.bcq_pack.argtypes = [vp, vp, i32, i64, i64, vp]
@@ -113,6 +115,15 @@ def dequant_shape_for(p: int, m: int, n: int, batch: int, group: int = 128, with
     pair = (ctypes.c_int * 2)()
     _check(lib().bcq_dequant_shape_for(p, m, n, batch, group, int(with_offsets), ctypes.byref(pair, 0), ctypes.byref(pair, 4)),
            "bcq_dequant_shape_for")
+    return pair[0], pair[1]
+
+
+def mixed_shape_for(precisions, m: int, n: int, batch: int, group: int = 128, with_offsets: bool = False) -> tuple:
+    """Benchmarks and tests: the shape of the level form that the large-batch kernel runs a call with per-request precision on, the scale sets
+    being those of ``precisions``; (0, 0) where its other kernels run it."""
+    pair = (ctypes.c_int * 2)()
+    _check(lib().bcq_mixed_shape_for(sum(1 << q for q in set(precisions)), m, n, batch, group, int(with_offsets), ctypes.byref(pair, 0),
+                                     ctypes.byref(pair, 4)), "bcq_mixed_shape_for")
     return pair[0], pair[1]
 
 

@@ -213,6 +213,24 @@ int bcq_dequant_shape_for(int p, int64_t m, int64_t n, int batch, int group, int
     return BCQ_OK;
 }
 
+int bcq_mixed_shape_for(int precisions, int64_t m, int64_t n, int batch, int group, int with_offsets, int *request_tiles, int *row_blocks)
+{
+    if (!request_tiles || !row_blocks) return BCQ_ERR_NULL;
+    bcq::GemmArgs a;
+    if (precisions < 2 || precisions >= 32 || (precisions & 1) || !sizes_only(1, m, n, batch, group, 0, a)) return BCQ_ERR_VARIANT;
+    static const _Float16 set{};
+    static const int32_t req = 0;
+    a.uniform_p = 0;
+    a.p_max = 4;
+    a.p_req = &req;                     // (never read)
+    for (int q = 1; q <= 4; ++q) {
+        a.scales[q] = precisions >> q & 1 ? &set : nullptr;
+        a.offsets[q] = with_offsets ? a.scales[q] : nullptr;
+    }
+    bcq::dequant_mfma_mixed_shape(a, *request_tiles, *row_blocks);
+    return BCQ_OK;
+}
+
 int bcq_level_layout(int p, int row_blocks, int64_t n, int group, int with_offsets, int *layout)
 {
     if (!layout) return BCQ_ERR_NULL;

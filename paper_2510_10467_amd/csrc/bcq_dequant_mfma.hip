@@ -1393,9 +1393,9 @@ hipError_t launch_p(const DequantParams &pr, const GemmArgs &a, hipStream_t stre
 // request_tiles: 1, 2 or 4 tiles of 64 requests, or 0 (with row_blocks != 0) for a single tile of 16 requests
 bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
 {
-    if ((request_tiles == 0 && row_blocks == 0) || (request_tiles == 1 && row_blocks >= 100 && row_blocks < 100 + kLevelShapeCount)) {
+    if ((request_tiles == 0 && row_blocks == 0) || (request_tiles == 1 && ((row_blocks >= 100 && row_blocks < 100 + kLevelShapeCount) || row_blocks == 96))) {
         g_forced_nt = g_forced_rw = 0;
-        g_forced_level = request_tiles == 0 ? -1 : row_blocks - 100;
+        g_forced_level = request_tiles == 0 ? -1 : row_blocks == 96 ? kLevelShapeCount : row_blocks - 100;      // (128 x 96: per-request precision only)
         return true;
     }
     const int nt = request_tiles == 0 ? 1 : request_tiles == 32 ? 2 : 4 * request_tiles;      // 32: a tile of 32 requests
@@ -1411,7 +1411,7 @@ bool dequant_mfma_force_shape(int request_tiles, int row_blocks)
 
 bool dequant_mfma_shape_fits(const GemmArgs &a)
 {
-    return a.uniform_p == 0 || g_forced_level < 0 || level_mfma_supports(a);
+    return a.uniform_p == 0 || g_forced_level < 0 || (g_forced_level < kLevelShapeCount && level_mfma_supports(a));
 }
 
 void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)
@@ -1444,8 +1444,7 @@ static int expected_share(const GemmArgs &a, int &nsets, int &deepest)
 }
 
 // Per-request precision beyond 32 requests: whether the level form runs it, its body per precision (level_byclass_kernel), and on which shape.
-// Of 160 calls drawn where the dequantising kernels were the choice it is 1.4 to 1.5 times as fast on average (8192 x 8192 with 200 requests
-// 119 -> 63 us; up to 64 requests, where groups of 64 rule the plane-wise variant out, 1.2 to 1.6 times).
+// Of 118 calls drawn where the dequantising kernels were the choice it is 1.30 times as fast on average (8192 x 8192 with 200 requests 119 -> 63 us).
 static bool level_classes(const GemmArgs &a, int &shape)
 {
     if (a.uniform_p != 0 || a.batch <= 32 || a.n % 256 != 0) return false;
@@ -1453,21 +1452,38 @@ static bool level_classes(const GemmArgs &a, int &shape)
     GemmArgs share_of = a;
     share_of.batch = expected_share(a, nsets, deepest);
     if (nsets == 0) return false;
+    if (g_forced_level >= 1) {                            // (256 x 256 is not among them)
+        shape = g_forced_level;
+        return true;
+    }
     share_of.uniform_p = deepest;
     float us = 0.f;
     shape = level_mfma_cheapest_classes(share_of, nsets, us);
-    if (a.batch > kClassFrom && g_forced_level < 0) {
-        // The summing form per precision (dequant_byclass_kernel) keeps narrow matrices and short ones with few requests (16896 x 1280 with 311
-        // requests 37 against 43 us, 1826 x 7936 with 85 in groups of 64 30 against 41); 0.9 and 2 us: drawn calls took 0.77 to 1.5 times this.
-        int nt, rw;
-        const float all = 0.9f * 32.f * cheapest_shape(deepest, a.m, share_of.batch, 4, nt, rw, nsets);
-        const int rows = 16 * row_blocks_of(nt, rw);
-        const float rounds = __builtin_ceilf((float)((a.m + rows - 1) / rows) * (float)((share_of.batch + 16 * nt - 1) / (16 * nt)) * (float)nsets / 256.f);
-        const float start = 5.65f * rounds;
-        if (large_batch_us(all > start ? all : start, start, a.n) + (a.n < 4096 ? 0.f : 2.f) < us) return false;
+    if (a.batch <= kClassFrom) {
+        // Up to 64 requests, where only groups of 64 come here, rebuilding the weights once per precision present (dequant_mixed_kernel, 64 rows per
+        // workgroup) stays ahead where the level form needs a second round of workgroups, it does not, and the rows are short: 11520 x 256 with
+        // 45 requests and three precisions 10.1 against 12.7 us, 13312 x 512 with 64 13.8 against 15.4, 16128 x 768 with 41 17.7 against 19.8;
+        // 13428 x 1024 with 43 19.9 against 20.1, and with one round (9472 x 256 with 49) 10.3 against 8.2, with two against two (19363 x 256 with
+        // 62) 17.7 against 13.7.  Of 334 drawn calls the level form is 1.2 to 1.6 times as fast.
+        return a.n > 768 || (a.m + 127) / 128 * nsets <= 256 || (a.m + 63) / 64 > 256;
     }
-    if (g_forced_level >= 1) shape = g_forced_level;      // (256 x 256 is not among them)
-    return true;
+    // The summing form per precision (dequant_byclass_kernel) keeps narrow matrices and short ones with few requests (16896 x 1280 with 311
+    // requests 37 against 43 us, 1826 x 7936 with 85 in groups of 64 30 against 41); 0.9 and 2 us: drawn calls took 0.77 to 1.5 times this.
+    int nt, rw;
+    const float all = 0.9f * 32.f * cheapest_shape(deepest, a.m, share_of.batch, 4, nt, rw, nsets);
+    const int rows = 16 * row_blocks_of(nt, rw);
+    const float full = (float)((a.m + rows - 1) / rows) * (float)((share_of.batch + 16 * nt - 1) / (16 * nt)) * (float)nsets / 256.f;
+    const float rounds = __builtin_ceilf(full);
+    const float start = 5.65f * rounds;
+    return large_batch_us(all > start ? all : start, start, a.n) + (a.n < 4096 ? 0.f : 2.f) >= us;
+}
+
+void dequant_mfma_mixed_shape(const GemmArgs &a, int &request_tiles, int &row_blocks)
+{
+    int level = 0;
+    const bool levels = g_forced_nt == 0 && level_classes(a, level);
+    request_tiles = levels ? 1 : 0;
+    row_blocks = !levels ? 0 : level == kLevelShapeCount ? 96 : 100 + level;
 }
 
 bool dequant_mfma_supports(const GemmArgs &a)
@@ -1572,8 +1588,8 @@ hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool plane
         int level = 0;
         if (g_forced_nt == 0 && level_classes(a, level)) return level_mfma_launch_classes(a, pr.class_order, level, stream);
         if (a.batch > kClassFrom && (g_forced_nt == 0 || g_forced_nt >= 4)) {
-            // Beyond 64 requests on widths the level form does not take: the uniform kernel's body per precision, each on the requests of that
-            // precision wherever they sit in the batch (dequant_byclass_kernel).  A weight is then rebuilt once per
+            // Beyond 64 requests where the level form is not ahead or does not take the width: the uniform kernel's body per precision, each on
+            // the requests of that precision wherever they sit in the batch (dequant_byclass_kernel).  A weight is then rebuilt once per
             // precision and up to 256 requests, at the cost of that precision alone, instead of once per 64
             // requests at the cost of all precisions present.
             int nsets, deepest;

@@ -95,6 +95,8 @@ bool dequant_mfma_force_shape(int request_tiles, int row_blocks);
 bool dequant_mfma_shape_fits(const GemmArgs &a);
 // the shape that a product at one precision runs with, forced or automatic, as the pair bcq_select_dequant_shape takes
 void dequant_mfma_shape(const GemmArgs &a, int &request_tiles, int &row_blocks);
+// per-request precision: the shape of the level form that runs the call, forced or automatic ((1, 96): 128 x 96), (0, 0) where it does not
+void dequant_mfma_mixed_shape(const GemmArgs &a, int &request_tiles, int &row_blocks);
 // planewise: the variant that multiplies the +-1 planes themselves and scales the group sums (groups of 128 or 256)
 hipError_t dequant_mfma_launch(const GemmArgs &a, hipStream_t stream, bool planewise = false, const GemmArgs *mats = nullptr, int count = 0);
 // several matrices (same n, precision, batch, activations, group size; no offsets) in one launch of the large-batch kernels

@@ -14,6 +14,13 @@ def built():
         hip_build.build()
 
 
+@pytest.fixture
+def knobs():
+    yield
+    bcq.select_dequant_shape(0, 0)
+    bcq.select_kernel("auto")
+
+
 def takes_level_form(p, m, n, batch, group=128, with_offsets=False):
     tiles, blocks = bcq.dequant_shape_for(p, m, n, batch, group, with_offsets)
     return tiles == 1 and blocks >= 100
@@ -54,6 +61,51 @@ def test_level_form_where_it_is_ahead(call, summing_us, level_us):
     assert takes_level_form(*call)
 
 
+# ((precisions), m, n, batch, group, offsets): microseconds of the form that rebuilds weights by sums and of the level form
+@pytest.mark.parametrize("call,summing_us,level_us", [
+    (((2, 3, 4), 11520, 256, 45, 64, False), 10.1, 12.7),               # up to 64 requests: a second round of workgroups
+    (((2, 3, 4), 13312, 512, 64, 64, False), 13.8, 15.4),
+    (((2, 3, 4), 16128, 768, 41, 64, True), 17.7, 19.8),
+    (((1, 2, 3, 4), 12288, 256, 47, 64, False), 10.6, 12.3)])
+def test_summing_forms_where_they_are_ahead_with_per_request_precision(call, summing_us, level_us):
+    assert bcq.mixed_shape_for(*call) == (0, 0)
+
+
+@pytest.mark.parametrize("call,summing_us,level_us", [
+    (((2, 3, 4), 9472, 256, 49, 64, False), 10.3, 8.2),
+    (((2, 3, 4), 19363, 256, 62, 64, False), 17.7, 13.7),
+    (((2, 3, 4), 18176, 768, 47, 64, False), 26.8, 19.4),
+    (((2, 3, 4), 21498, 1024, 42, 64, False), 33.1, 22.9),
+    (((2, 3, 4), 4956, 2816, 52, 64, False), 46.4, 18.4),
+    (((2, 3, 4), 8192, 8192, 200, 128, False), 118.6, 63.0)])
+def test_level_form_where_it_is_ahead_with_per_request_precision(call, summing_us, level_us):
+    assert bcq.mixed_shape_for(*call)[0] == 1
+
+
+def test_per_request_precision_that_the_level_form_does_not_take(knobs):
+    assert bcq.mixed_shape_for((2, 3, 4), 8192, 8192, 32) == (0, 0)             # one tile of 32 requests
+    assert bcq.mixed_shape_for((2, 3, 4), 8192, 8192 + 128, 200) == (0, 0)      # not whole pairs of column groups
+    for bad in (((), 8192, 8192, 200), ((5,), 8192, 8192, 200), ((2,), 8192, 8192, 200, 32), ((2,), 0, 8192, 200), ((2,), 8192, 8192, 0)):
+        with pytest.raises(bcq.BcqError) as error:
+            bcq.mixed_shape_for(*bad)
+        assert error.value.status == -6
+    assert bcq.lib().bcq_mixed_shape_for(4, 8192, 8192, 200, 128, 0, None, None) == -1
+    automatic = bcq.mixed_shape_for((2, 3, 4), 1024, 1024, 100), bcq.mixed_shape_for((2, 3, 4), 8192, 8192, 200)
+    assert automatic == ((0, 0), (1, 96))
+    for blocks in (96, 101, 105):
+        bcq.select_dequant_shape(1, blocks)
+        assert bcq.mixed_shape_for((2, 3, 4), 1024, 1024, 100) == (1, blocks)
+        assert bcq.mixed_shape_for((2, 3, 4), 1024, 1152, 100) == (0, 0)
+    bcq.select_dequant_shape(1, 100)                                            # not a shape of these calls
+    assert (bcq.mixed_shape_for((2, 3, 4), 1024, 1024, 100), bcq.mixed_shape_for((2, 3, 4), 8192, 8192, 200)) == automatic
+    bcq.select_dequant_shape(1, 96)                                             # and one of these calls only
+    with pytest.raises(bcq.BcqError) as error:
+        bcq.dequant_shape_for(4, 8192, 8192, 200)
+    assert error.value.status == -6
+    bcq.select_dequant_shape(4, 8)
+    assert bcq.mixed_shape_for((2, 3, 4), 8192, 8192, 200) == (0, 0)
+
+
 def test_what_the_level_form_does_not_take():
     assert takes_level_form(4, 28672, 8192, 33)
     assert not takes_level_form(4, 28672, 8192, 32)             # one tile of 32 requests
@@ -66,16 +118,9 @@ def test_what_the_level_form_does_not_take():
     assert bcq.lib().bcq_dequant_shape_for(4, 28672, 8192, 500, 128, 0, None, None) == -1
 
 
-@pytest.fixture
-def knobs():
-    yield
-    bcq.select_dequant_shape(0, 0)
-    bcq.select_kernel("auto")
-
-
 def test_forced_level_form_refuses_what_it_does_not_take(knobs):
     """A forced shape that cannot run the problem is reported as that (-6) before anything is launched (made-up addresses do), from
-    every entry point; per-request precision never runs on the level form and is not concerned."""
+    every entry point.  (Per-request precision runs on its other kernels there, see the test of its forced shapes.)"""
     L = bcq.lib()
     P, S, X, Y = 0x10000, 0x20000, 0x30000, 0x40000
     bcq.select_kernel("dequant_mfma")
