@@ -1294,6 +1294,16 @@ float cheapest_shape(int p, int64_t m, int batch, int min_nt, int &nt, int &rw, 
     return best;
 }
 
+// What `full` times 256 workgroups of a shape cost, in rounds of 256.
+float rounds_of(int nt, int rw, float full, int64_t n)
+{
+    if (nt != 8 || rw != 8 || full <= 1.f || n > 4096) return __builtin_ceilf(full);
+    // 64 KiB of LDS: two workgroups on a CU, a second one at half to three quarters of the first (16655 x 1024 with 276 requests, 393
+    // workgroups: 31.3 us where two rounds would take 37.6); on longer rows as for the tiles of 128 x 64 of the level form
+    const float pairs = __builtin_floorf(full / 2.f), rest = full - 2.f * pairs;
+    return 1.75f * pairs + (rest == 0.f ? 0.f : rest <= 1.f ? 1.f : 1.5f + 0.25f * (rest - 1.f));
+}
+
 // What a product above 32 requests is expected to take with its cheapest shape, in microseconds.  start_us: the part of a round
 // that does not depend on the width.
 float summing_us(const GemmArgs &a)
@@ -1303,15 +1313,8 @@ float summing_us(const GemmArgs &a)
     float all = 32.f * cheapest_shape(a.uniform_p, a.m, a.batch, 1, nt, rw);
     const int rows = 16 * row_blocks_of(nt, rw);
     const float full = (float)((a.m + rows - 1) / rows) * (float)((a.batch + 16 * nt - 1) / (16 * nt)) / 256.f;
-    float rounds = __builtin_ceilf(full);
-    if (nt == 8 && rw == 8 && full > 1.f && a.n <= 4096) {
-        // 64 KiB of LDS: two workgroups on a CU, a second one at half to three quarters of the first (16655 x 1024 with 276 requests, 393
-        // workgroups: 31.3 us where two rounds would take 37.6); on longer rows as for the tiles of 128 x 64 of the level form
-        const float pairs = __builtin_floorf(full / 2.f), rest = full - 2.f * pairs;
-        const float price = 1.75f * pairs + (rest == 0.f ? 0.f : rest <= 1.f ? 1.f : 1.5f + 0.25f * (rest - 1.f));
-        all *= price / rounds;
-        rounds = price;
-    }
+    const float rounds = rounds_of(nt, rw, full, a.n);
+    if (full > 1.f) all *= rounds / __builtin_ceilf(full);
     return large_batch_us(all, rounds * start_us, a.n);
 }
 
@@ -1468,12 +1471,14 @@ static bool level_classes(const GemmArgs &a, int &shape)
         return a.n > 768 || (a.m + 127) / 128 * nsets <= 256 || (a.m + 63) / 64 > 256;
     }
     // The summing form per precision (dequant_byclass_kernel) keeps narrow matrices and short ones with few requests (16896 x 1280 with 311
-    // requests 37 against 43 us, 1826 x 7936 with 85 in groups of 64 30 against 41); 0.9 and 2 us: drawn calls took 0.77 to 1.5 times this.
+    // requests 37 against 43 us, 1826 x 7936 with 85 in groups of 64 30 against 41, 17433 x 768 with 196 25.5 against 33.4); 0.9 and 2 us:
+    // drawn calls took 0.77 to 1.5 times this.
     int nt, rw;
-    const float all = 0.9f * 32.f * cheapest_shape(deepest, a.m, share_of.batch, 4, nt, rw, nsets);
+    float all = 0.9f * 32.f * cheapest_shape(deepest, a.m, share_of.batch, 4, nt, rw, nsets);
     const int rows = 16 * row_blocks_of(nt, rw);
     const float full = (float)((a.m + rows - 1) / rows) * (float)((share_of.batch + 16 * nt - 1) / (16 * nt)) * (float)nsets / 256.f;
-    const float rounds = __builtin_ceilf(full);
+    const float rounds = rounds_of(nt, rw, full, a.n);
+    if (full > 1.f) all *= rounds / __builtin_ceilf(full);
     const float start = 5.65f * rounds;
     return large_batch_us(all > start ? all : start, start, a.n) + (a.n < 4096 ? 0.f : 2.f) >= us;
 }

@@ -66,7 +66,9 @@ def test_level_form_where_it_is_ahead(call, summing_us, level_us):
     (((2, 3, 4), 11520, 256, 45, 64, False), 10.1, 12.7),               # up to 64 requests: a second round of workgroups
     (((2, 3, 4), 13312, 512, 64, 64, False), 13.8, 15.4),
     (((2, 3, 4), 16128, 768, 41, 64, True), 17.7, 19.8),
-    (((1, 2, 3, 4), 12288, 256, 47, 64, False), 10.6, 12.3)])
+    (((1, 2, 3, 4), 12288, 256, 47, 64, False), 10.6, 12.3),
+    (((2, 3, 4), 17433, 768, 196, 64, False), 25.5, 33.4),              # beyond: two workgroups of 128 x 128 on a CU
+    (((2, 3, 4), 21760, 768, 228, 64, False), 30.2, 42.1)])
 def test_summing_forms_where_they_are_ahead_with_per_request_precision(call, summing_us, level_us):
     assert bcq.mixed_shape_for(*call) == (0, 0)
 
