@@ -2,7 +2,8 @@
 
 Argument marshalling only: every step of the product runs in the HIP kernels.
 The product calls are marshalled by ``_bcq_host`` (``csrc/bcq_host.cpp``) where everything about a call is as it should
-be; the Python code below is what makes the other calls, or says what is wrong with them.
+be; the Python code below is what makes the other calls, or says what is wrong with them.  It makes all of them, with a warning, where
+``_bcq_host`` was not built for the Python and torch that run.
 PyTorch supplies device memory and the current stream.  There is no CPU
 fallback: if the shared library is missing the import of this module's
 functions raises, and every call checks that its tensors live on the GPU.
@@ -11,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
@@ -28,6 +30,25 @@ class BcqError(RuntimeError):
     def __init__(self, status: int, where: str):
         self.status = status
         super().__init__(f"{where}: {lib().bcq_strerror(status).decode()} (status {status})")
+
+
+class _NoHost:
+    """In the place of ``_bcq_host``: declines every call, so that the Python code makes it."""
+    gemv = gemv_multi = gemm_mixed = staticmethod(lambda *args: None)
+
+
+def _load_host(functions):
+    """``_bcq_host``, bound to the library's functions: it holds torch's inline code and so fits one Python and one torch only."""
+    try:
+        from . import _bcq_host as host
+        if host.torch_version != torch.__version__:
+            raise ImportError(f"built for torch {host.torch_version}, this is {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"_bcq_host does not load ({e}); calls from Python take about 5 us longer until the package is built again "
+                      "(`python paper_2510_10467_amd/build.py`)", RuntimeWarning, stacklevel=3)
+        return _NoHost
+    host.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in functions), BcqError)
+    return host
 
 
 def lib() -> ctypes.CDLL:
@@ -73,9 +94,7 @@ def lib() -> ctypes.CDLL:
         for f in (L.bcq_select_kernel, L.bcq_pack, L.bcq_unpack, L.bcq_gemv, L.bcq_gemm_mixed, L.bcq_gemv_offset,
                   L.bcq_gemm_mixed_offset):
             f.restype = i32
-        from . import _bcq_host
-        _bcq_host.bind(*(ctypes.cast(f, vp).value for f in (L.bcq_gemv_offset, L.bcq_gemv_multi, L.bcq_gemm_mixed, L.bcq_gemm_mixed_offset)), BcqError)
-        _host = _bcq_host
+        _host = _load_host((L.bcq_gemv_offset, L.bcq_gemv_multi, L.bcq_gemm_mixed, L.bcq_gemm_mixed_offset))
         _lib = L
     return _lib
 

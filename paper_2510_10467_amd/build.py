@@ -1,4 +1,4 @@
-"""Builds in-tree: csrc/*.hip -> libbcq_hip.so for gfx950, and csrc/bcq_host.cpp -> _bcq_host.so, the binding's host code."""
+"""Builds in-tree: csrc/*.hip -> libbcq_hip.so for gfx950, and csrc/bcq_host.cpp -> _bcq_host, the binding's host code."""
 from __future__ import annotations
 
 import glob
@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbcq_hip.so")
 HOST_SOURCE = os.path.join(CSRC, "bcq_host.cpp")
-HOST_LIB = os.path.join(HERE, "_bcq_host.so")
+HOST_LIB = os.path.join(HERE, "_bcq_host" + sysconfig.get_config_var("EXT_SUFFIX"))      # (another Python does not see it)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
@@ -28,13 +28,22 @@ def sources():
 
 
 def is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(HOST_LIB):
-        return True
-    if os.path.getmtime(HOST_SOURCE) > os.path.getmtime(HOST_LIB):
+    if not os.path.exists(LIB) or host_is_stale():
         return True
     t = os.path.getmtime(LIB)
     deps = sources() + glob.glob(os.path.join(CSRC, "*.hpp")) + glob.glob(os.path.join(ROOT, "include", "*.h"))
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def host_is_stale() -> bool:
+    """Missing for this Python, older than its source, or built against another torch."""
+    import torch
+    if not os.path.exists(HOST_LIB):
+        return True
+    if max(os.path.getmtime(f) for f in (HOST_SOURCE, os.path.join(ROOT, "include", "bcq.h"))) > os.path.getmtime(HOST_LIB):
+        return True
+    with open(HOST_LIB, "rb") as f:
+        return f"built for torch {torch.__version__}\0".encode() not in f.read()
 
 
 def build(verbose: bool = False) -> str:
@@ -68,7 +77,7 @@ def build_host(verbose: bool = False) -> str:
     import torch
     torch_dir = os.path.dirname(torch.__file__)
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f'-DBCQ_TORCH_VERSION="{torch.__version__}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
            "-I", os.path.join(ROOT, "include"), "-isystem", os.path.join(torch_dir, "include"), "-isystem", "/opt/rocm/include",
            "-isystem", sysconfig.get_paths()["include"], "-o", HOST_LIB, HOST_SOURCE,
            "-L", os.path.join(torch_dir, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]

@@ -264,4 +264,12 @@ PyModuleDef g_module = {PyModuleDef_HEAD_INIT, "_bcq_host", nullptr, -1, g_metho
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__bcq_host(void) { return PyModule_Create(&g_module); }
+// the torch this was built against, as torch.__version__ has it: another one's tensors may be laid out differently
+constexpr char kBuiltFor[] = "built for torch " BCQ_TORCH_VERSION;
+
+PyMODINIT_FUNC PyInit__bcq_host(void)
+{
+    PyObject *module = PyModule_Create(&g_module);
+    if (module && PyModule_AddStringConstant(module, "torch_version", kBuiltFor + sizeof "built for torch " - 1) != 0) Py_CLEAR(module);
+    return module;
+}

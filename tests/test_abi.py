@@ -3,6 +3,9 @@ symbol the header declares, and rejects bad arguments before touching the device
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import sysconfig
 
 import pytest
 
@@ -201,3 +204,50 @@ def test_pack_rejects_what_one_grid_cannot_hold(lib):
     assert lib.bcq_pack(C, P, 4, ctypes.c_int64(1 << 33), ctypes.c_int64(4096), None) == -3
     assert lib.bcq_unpack(P, C, 8, ctypes.c_int64(1 << 36), ctypes.c_int64(32), None) == -3
     assert lib.bcq_pack(C, P, 1, ctypes.c_int64(1 << 41), ctypes.c_int64(32), None) == -3
+
+
+# What a process finds that was not built anew: no host code at all, one of another torch, one that does not load
+HOST_CODE = {"missing": "sys.modules['paper_2510_10467_amd._bcq_host'] = None",
+             "of another torch": "sys.modules['paper_2510_10467_amd._bcq_host'] = types.SimpleNamespace(torch_version='0.1')",
+             "that does not load": "sys.meta_path.insert(0, Broken())"}
+
+
+@pytest.mark.parametrize("which", HOST_CODE)
+def test_the_library_works_without_the_host_code(lib, which):
+    """Only the product calls go through the host code, and the Python code behind it can make those too: nothing else depends on it."""
+    code = f"""
+import sys, types, warnings
+class Broken:
+    def find_spec(self, name, path=None, target=None):
+        if name.endswith("_bcq_host"):
+            raise ImportError("undefined symbol")
+{HOST_CODE[which]}
+import torch
+import paper_2510_10467_amd as bcq
+with warnings.catch_warnings(record=True) as said:
+    warnings.simplefilter("always")
+    assert bcq.lib().bcq_strerror(0) == b"ok"
+assert [w.category for w in said] == [RuntimeWarning] and "build.py" in str(said[0].message)
+planes, x = torch.zeros((4, 8, 4), dtype=torch.int32), torch.zeros((1, 128), dtype=torch.float16)
+scales = torch.zeros((2, 8, 1), dtype=torch.float16)
+for call in (lambda: bcq.bcq_gemv(planes, scales, 2, x), lambda: bcq.bcq_gemv_multi([planes], [scales], 2, x),
+             lambda: bcq.bcq_gemm_mixed(planes, {{2: scales}}, torch.zeros(1, dtype=torch.int32), x), lambda: bcq.bcq_unpack(planes)):
+    try:
+        call()
+    except TypeError as e:
+        assert "must be a GPU tensor" in str(e), e
+    else:
+        raise AssertionError("a CPU tensor was taken")
+"""
+    done = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
+
+
+def test_host_code_of_another_torch_or_python_is_stale(lib, monkeypatch):
+    import torch
+
+    from paper_2510_10467_amd import build as hip_build
+    assert not hip_build.host_is_stale()
+    assert hip_build.HOST_LIB.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + "1")
+    assert hip_build.host_is_stale() and hip_build.is_stale()
