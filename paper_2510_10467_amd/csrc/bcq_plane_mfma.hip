@@ -1070,22 +1070,21 @@ hipError_t launch_pair(const PlaneMfmaParams &pr, const Plan &pl, dim3 grid, dim
 template <int NB, bool OFFSET, int GS>
 hipError_t launch_group(const GemmArgs &a, const PlaneMfmaParams &pr, const Plan &pl, dim3 grid, dim3 block, hipStream_t stream)
 {
-    if constexpr (NB == 1) {
-        if (a.batch == 1 && a.uniform_p > 0) {
-            switch (a.uniform_p) {
-            case 1: return launch_single<1, OFFSET, GS>(pr, pl, grid, block, stream);
-            case 2: return launch_single<2, OFFSET, GS>(pr, pl, grid, block, stream);
-            case 3: return launch_single<3, OFFSET, GS>(pr, pl, grid, block, stream);
-            default: return launch_single<4, OFFSET, GS>(pr, pl, grid, block, stream);
-            }
-        }
-    }
     if (a.uniform_p == 0) return launch_one(plane_mfma_kernel<kMaxP, NB, true, OFFSET, false, GS>, pr, pl, grid, block, stream);
-    switch (a.uniform_p) {
-    case 1: return launch_one(plane_mfma_kernel<1, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
-    case 2: return launch_one(plane_mfma_kernel<2, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
-    case 3: return launch_one(plane_mfma_kernel<3, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
-    default: return launch_one(plane_mfma_kernel<4, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
+    if constexpr (NB == 1) {                    // one request (make_plan)
+        switch (a.uniform_p) {
+        case 1: return launch_single<1, OFFSET, GS>(pr, pl, grid, block, stream);
+        case 2: return launch_single<2, OFFSET, GS>(pr, pl, grid, block, stream);
+        case 3: return launch_single<3, OFFSET, GS>(pr, pl, grid, block, stream);
+        default: return launch_single<4, OFFSET, GS>(pr, pl, grid, block, stream);
+        }
+    } else {
+        switch (a.uniform_p) {
+        case 1: return launch_one(plane_mfma_kernel<1, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
+        case 2: return launch_one(plane_mfma_kernel<2, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
+        case 3: return launch_one(plane_mfma_kernel<3, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
+        default: return launch_one(plane_mfma_kernel<4, NB, false, OFFSET, false, GS>, pr, pl, grid, block, stream);
+        }
     }
 }
 
@@ -1382,7 +1381,7 @@ hipError_t plane_mfma_launch_multi(const GemmArgs *mats, int count, hipStream_t 
     pr.inv_span = 1.0f / (float)(8 * pr.ntiles);
     pr.inv_ks = 1.0f / (float)pl.KS;
     dim3 block(64 * pl.KS);
-    if (pl.NB == 1 && count == 2 && a.batch == 1) {
+    if (pl.NB == 1 && count == 2) {
         switch (a.uniform_p) {
         case 1: return launch_pair<1>(pr, pl, grid, block, stream);
         case 2: return launch_pair<2>(pr, pl, grid, block, stream);

@@ -55,3 +55,9 @@ def test_two_workgroups_of_the_128_x_64_tiles_share_a_cu(kernels):
             for group in (64, 128, 256):
                 used = bcq.level_layout(p, 104, 4096, group, offsets)["lds_bytes"]
                 assert 2 * used <= 160 * 1024, f"p={p} offsets={offsets} group={group}: {used} bytes of LDS"
+
+
+def test_one_request_at_one_precision_has_one_kernel(kernels):
+    """plane_mfma_kernel<P, 1, false, .., false, ..> is what plane_mfma_single_kernel replaced: nothing launches it."""
+    assert not [name for name in kernels if re.search(r"plane_mfma_kernelILi\dELi1ELb0ELb[01]ELb0E", name)]
+    assert len([name for name in kernels if "plane_mfma_single_kernel" in name]) == 4 * 2 * 3       # planes, offsets, group sizes
