@@ -150,7 +150,10 @@ def test_products_that_are_exact(gpu, force, shape):
         assert torch.equal(y, bcq.bcq_gemv(other, dl.scales[p], p, x)), f"shape {shape} p={p}: planes >= p influenced the result"
 
 
-@pytest.mark.parametrize("shape", [(1, 101), (1, 102), (1, 103), (1, 104), (1, 105), (0, 0)])
+PER_REQUEST = [(1, 96), (1, 101), (1, 102), (1, 103), (1, 104), (1, 105)]         # the first: 128 x 96, of these calls only
+
+
+@pytest.mark.parametrize("shape", PER_REQUEST + [(0, 0)])
 @pytest.mark.parametrize("m,n,batch,group", [(150, 1280, 33, 128), (70, 768, 129, 64), (259, 1536, 300, 256)])
 def test_per_request_precision(gpu, force, shape, m, n, batch, group):
     """The form per precision, its requests wherever they sit in the batch: with offsets for some precisions and without, a precision without
@@ -160,12 +163,14 @@ def test_per_request_precision(gpu, force, shape, m, n, batch, group):
     x = syn.make_x(batch, n, seed=(961, batch))
     p_req = syn.make_p_req(batch, 1, 4, seed=(962, batch))
     some = {q: syn.make_offsets(q, m, n, group, seed=(963, q)) for q in (2, 4)}
+    import paper_2510_10467_amd as bcq
+    force(shape)
+    assert shape == (0, 0) or bcq.mixed_shape_for((1, 2, 3, 4), m, n, batch, group) == shape
     for req in (p_req, np.full(batch, 3, dtype=np.int32)):
         for z in (None, some):
             force(shape)
             used, _ = gpu.check_mixed(dl, req, x, "dequant_mfma", group, offsets_by_p=z)
             assert used == "dequant_mfma"
-    import paper_2510_10467_amd as bcq
     force(shape)
     x_dev = gpu.to_dev(x)
     y = bcq.bcq_gemm_mixed(dl.planes, dl.scales, gpu.to_dev(p_req), x_dev, group=group).cpu().numpy()
@@ -176,20 +181,49 @@ def test_per_request_precision(gpu, force, shape, m, n, batch, group):
     assert not z[p_req == 2].any() and np.array_equal(z[p_req != 2], y[p_req != 2])
 
 
-def test_per_request_precision_on_tiles_of_96(gpu):
+@pytest.mark.parametrize("shape", PER_REQUEST)
+@pytest.mark.parametrize("group", [64, 128, 256])
+def test_every_weight_with_per_request_precision(gpu, force, group, shape):
+    """One-hot activations of 4352 requests, each at a precision of its own, over 17 pairs of column groups: blocks of two pairs and a single one after
+    them, windows of scales that are loaded again, tiles of ranks that precisions leave ragged; offsets for two of the four precisions."""
+    import paper_2510_10467_amd as bcq
+    m, n = 67, 4352
+    layer = syn.make_layer(m, n, group=group, seed=(971, n, group), signed=True)
+    dl = gpu.DeviceLayer(layer)
+    x = gpu.to_dev(np.eye(n, dtype=np.float16))
+    p_req = syn.make_p_req(n, 1, 4, seed=(972, n))
+    some = {q: syn.make_offsets(q, m, n, group, seed=(973, q)) for q in (2, 4)}
+    force(shape)
+    assert bcq.mixed_shape_for((1, 2, 3, 4), m, n, n, group) == shape
+    for z in ({}, some):
+        w = {q: weights16(layer, q, group, z.get(q)) for q in (1, 2, 3, 4)}
+        expected = np.stack([w[q][:, b] for b, q in enumerate(p_req)]) + np.float16(0)
+        y = bcq.bcq_gemm_mixed(dl.planes, dl.scales, gpu.to_dev(p_req), x, group=group, offsets_by_p={q: gpu.to_dev(o) for q, o in z.items()})
+        assert bcq.last_kernel() == "dequant_mfma"
+        wrong = np.argwhere((y + 0.0).cpu().numpy().view(np.uint16) != expected.view(np.uint16))
+        assert wrong.size == 0, f"{len(wrong)} weights differ, first [column, row] {wrong[0]} at precision {p_req[wrong[0][0]]}"
+
+
+def test_per_request_precision_on_tiles_of_96(gpu, oracle):
     """Sizes that the automatic choice gives 128 rows x 96 requests; capture in a graph and replays give what the call gives."""
     import torch
 
     import paper_2510_10467_amd as bcq
-    m, n, batch = 6000, 512, 255
+    m, n, batch = 6000, 4352, 255
+    assert bcq.mixed_shape_for((2, 3, 4), m, n, batch) == (1, 96)
     layer = syn.make_layer(m, n, seed=(964, m), precisions=[2, 3, 4], signed=True)
     dl = gpu.DeviceLayer(layer)
     x = syn.make_x(batch, n, seed=(964, batch))
     p_req = syn.make_p_req(batch, 2, 4, seed=(964, 0))
-    used, _ = gpu.check_mixed(dl, p_req, x, "auto")
-    assert used == "dequant_mfma"
     x_dev, r_dev = gpu.to_dev(x), gpu.to_dev(p_req)
-    eager = bcq.bcq_gemm_mixed(dl.planes, dl.scales, r_dev, x_dev)
+    out = gpu.Guarded((batch, m))
+    eager = bcq.bcq_gemm_mixed(dl.planes, dl.scales, r_dev, x_dev, y=out.t)
+    assert bcq.last_kernel() == "dequant_mfma"
+    out.check("tiles of 96")
+    rows = np.unique(np.concatenate([[0, 127, 128, m - 1], np.random.default_rng([syn.BASE_SEED, 974]).integers(0, m, size=60)]))
+    y_ref, a_ref = oracle.gemm_mixed(np.ascontiguousarray(layer.planes[:, rows, :]), {q: np.ascontiguousarray(t[:, rows, :]) for q, t in layer.scales.items()},
+                                     p_req, x)
+    gpu.assert_within_tolerance(eager[:, rows], y_ref, a_ref, "tiles of 96")
     y = torch.empty_like(eager)
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
