@@ -708,31 +708,41 @@ hipError_t visit(int p, bool offset, F f)
     }
 }
 
+// (four planes with offsets have no room for words of two pairs)
+template <typename S, typename F>
+hipError_t visit_wide(int p, bool offset, F f)
+{
+    switch (p) {
+    case 1: return offset ? f(Kernel<1, S, true>{}) : f(Kernel<1, S, false>{});
+    case 2: return offset ? f(Kernel<2, S, true>{}) : f(Kernel<2, S, false>{});
+    case 3: return offset ? f(Kernel<3, S, true>{}) : f(Kernel<3, S, false>{});
+    default: return offset ? hipErrorInvalidValue : f(Kernel<4, S, false>{});
+    }
+}
+
 // f(the kernel that a product at one precision runs with on a shape).  Words for two pairs of groups at a time against one (200 workgroups, 1536 /
 // 3840 / 14336 columns in groups of 128, microseconds):
 //   128 x 128, p = 4   21.8 / 43.8 / 132    against  21.8 / 44.2 / 137: from three planes on
 //              p = 2   17.1 / 34.7 / 108    against  16.6 / 34.0 / 108: not at one and two
-//   64 x 128,  p = 4   14.9 / 27.9 / 83.0   against  14.1 / 27.6 / 83.4: never
-//   64 x 64,   p = 4   11.1 / 19.8 / 56.9   against  10.3 / 19.4 / 57.2: not at three and four
-//              p = 2   9.2 / 15.2 / 41.6    against  8.6 / 14.2 / 45: at one and two beyond 5120 columns
-// A workgroup starts with both pairs of its first block, and of five pairs two teams get two and one team one.
+//   64 x 128,  p = 4   14.9 / 27.9 / 83.0   against  14.1 / 27.6 / 83.4: beyond 5120 columns
+//              p = 3   13.6 / 25.2 / 74.1   against  12.9 / 24.5 / 76.6
+//   64 x 64,   p = 4   11.1 / 19.8 / 56.9   against  10.3 / 19.4 / 57.2: the same
+//              p = 2   9.2 / 15.2 / 41.6    against  8.6 / 14.2 / 45
+// A workgroup starts with both pairs of its first block, and of five pairs two teams get two and one team one: that is what narrow matrices lose.
 // (256 x 256 has no registers for it, 128 x 64 no LDS with two workgroups on a CU.)
+constexpr int64_t kBlocksBeyond = 5120;         // columns; 64 rows
+
 template <typename F>
 hipError_t visit_shape(int shape, int p, bool offset, int64_t n, F f)
 {
+    const bool wide = n > kBlocksBeyond && !(offset && p == 4);
     switch (shape) {
     case 0: return visit<Shape<8, 8, 1, 1, kNever>>(p, offset, f);
     case 1: return visit<Shape<4, 4, 2, 1, 3>>(p, offset, f);
     case 2: return visit<Shape<4, 4, 1, 2, 3>>(p, offset, f);
-    case 3: return visit<Shape<4, 2, 1, 2, kNever>>(p, offset, f);
+    case 3: return wide ? visit_wide<Shape<4, 2, 1, 2, 1>>(p, offset, f) : visit<Shape<4, 2, 1, 2, kNever>>(p, offset, f);
     case 4: return visit<Shape<2, 4, 1, 2, kNever>>(p, offset, f);
-    case 5:
-        if (p <= 2 && n > 5120) {
-            using Wide = Shape<2, 2, 1, 4, 1>;
-            if (p == 1) return offset ? f(Kernel<1, Wide, true>{}) : f(Kernel<1, Wide, false>{});
-            return offset ? f(Kernel<2, Wide, true>{}) : f(Kernel<2, Wide, false>{});
-        }
-        return visit<Shape<2, 2, 1, 4, kNever>>(p, offset, f);
+    case 5: return wide ? visit_wide<Shape<2, 2, 1, 4, 1>>(p, offset, f) : visit<Shape<2, 2, 1, 4, kNever>>(p, offset, f);
     default: return hipErrorInvalidValue;
     }
 }

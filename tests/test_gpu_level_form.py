@@ -108,20 +108,22 @@ def test_every_weight_on_narrow_matrices(gpu, force, n, group, with_offsets):
 
 @pytest.mark.parametrize("n,group", [(5376, 128), (6400, 64)])
 @pytest.mark.parametrize("with_offsets", [False, True])
-def test_every_weight_where_64_x_64_takes_words_for_two_pairs(gpu, force, n, group, with_offsets):
-    """One and two planes beyond 5120 columns: 21 and 25 pairs, whole blocks for every team and then five pairs or one."""
+def test_every_weight_where_tiles_of_64_rows_take_words_for_two_pairs(gpu, force, n, group, with_offsets):
+    """Beyond 5120 columns: 21 and 25 pairs, whole blocks for every team and then one pair, five or one."""
     import paper_2510_10467_amd as bcq
     m = 67
-    layer = syn.make_layer(m, n, p_max=2, group=group, seed=(976, n, group), precisions=[1, 2], signed=True)
+    layer = syn.make_layer(m, n, group=group, seed=(976, n, group), signed=True)
     dl = gpu.DeviceLayer(layer)
     x = gpu.to_dev(np.eye(n, dtype=np.float16))
-    force((1, 105))
-    for p in (1, 2):
+    for p in (1, 2, 3, 4):
         z = syn.make_offsets(p, m, n, group, seed=(977, n, p)) if with_offsets else None
+        z_dev = None if z is None else gpu.to_dev(z)
         expected = (weights16(layer, p, group, z).T + np.float16(0)).view(np.uint16)
-        y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x, group=group, offsets=None if z is None else gpu.to_dev(z))
-        wrong = np.argwhere((y + 0.0).cpu().numpy().view(np.uint16) != expected)
-        assert wrong.size == 0, f"p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
+        for shape in ((1, 103), (1, 105)):
+            force(shape)
+            y = bcq.bcq_gemv(dl.planes, dl.scales[p], p, x, group=group, offsets=z_dev)
+            wrong = np.argwhere((y + 0.0).cpu().numpy().view(np.uint16) != expected)
+            assert wrong.size == 0, f"shape {shape} p={p}: {len(wrong)} weights differ, first [column, row] {wrong[0]}"
 
 
 @pytest.mark.parametrize("shape", SHAPES)
