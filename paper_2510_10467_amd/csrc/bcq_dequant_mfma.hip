@@ -1322,11 +1322,11 @@ float summing_us(const GemmArgs &a)
 int level_shape_of(const GemmArgs &a)
 {
     if (g_forced_level >= 0) return g_forced_level;
-    // Above 32 requests (up to there its tiles stand partly empty) the level form wherever it is expected to be ahead.  Of 1200 products
-    // drawn from n = 256 .. 28672, m = 1024 .. 28672 and 33 to 1000 requests it takes 668, 1.25 times as fast as the summing form on
-    // average; 6 of them are more than 3 % slower, the worst 7262 x 18432 with 149 requests at p = 4, 138 -> 154 us.
-    // 28672 x 8192 at 2048 requests and p = 3: 1182 -> 917 us; 8192 x 8192 at 96 and p = 4: 48 -> 38; 4096 x 256 at 500 and
-    // p = 4, where the start of a round decides, stays (6.9 against 8.6).
+    // Above 32 requests (up to there its tiles stand partly empty) the level form wherever it is expected to be ahead.  Of 600 products
+    // drawn from n = 256 .. 28672, m = 1024 .. 28672 and 33 to 1000 requests it takes 375, 1.27 times as fast as the best summing shape on
+    // average and none more than 3 % slower; 19 of the others would be more than 3 % faster on it, most of them p = 4 with offsets
+    // (12544 x 25600 with 82 requests 187 against 154 us).  28672 x 8192 at 2048 requests and p = 3: 1182 -> 850 us; 8192 x 8192 at
+    // 96 and p = 4 in groups of 64: 48 -> 35; 4096 x 256 at 500 and p = 4, where the start of a round decides, stays (7.2 against 8.7).
     if (g_forced_nt != 0 || a.batch <= 32 || !level_mfma_supports(a)) return -1;
     float us = 0.f;
     const int shape = level_mfma_cheapest(a, us);
@@ -1447,7 +1447,7 @@ static int expected_share(const GemmArgs &a, int &nsets, int &deepest)
 }
 
 // Per-request precision beyond 32 requests: whether the level form runs it, its body per precision (level_byclass_kernel), and on which shape.
-// Of 118 calls drawn where the dequantising kernels were the choice it is 1.30 times as fast on average (8192 x 8192 with 200 requests 119 -> 63 us).
+// Of 118 calls drawn where the dequantising kernels were the choice it is 1.30 times as fast on average (8192 x 8192 with 200 requests 119 -> 62 us).
 static bool level_classes(const GemmArgs &a, int &shape)
 {
     if (a.uniform_p != 0 || a.batch <= 32 || a.n % 256 != 0) return false;

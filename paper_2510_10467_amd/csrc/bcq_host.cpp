@@ -1,11 +1,11 @@
 // The host side of a product call from Python: argument checks, the output tensor, the current stream and the call into the C
 // ABI, without a Python-level step in between.  From Python the same takes about 5 us more per call (tensor attributes
 // read one by one, torch.empty, a Stream object, ctypes), more than the kernel of a small projection: 1024 x 4096 with one
-// request, called over and over, 9.1 -> 4.4 us a call (its kernel 3.6), the four calls of a Llama-3-8B block's linear layers with four
+// request, called over and over, 9.1 -> 4.4 us a call (its kernel 2.8), the four calls of a Llama-3-8B block's linear layers with four
 // requests 53 -> 30 us.
 //
-// Every function takes the call only if everything about it is as it should be, and returns None otherwise: the
-// Python code behind it then makes the same checks again and raises what it always raised.  Nothing is kept between calls.
+// Every function takes the call only if everything about it is as it should be (plain tensors, ints, lists, dicts; several matrices only with
+// new results), and returns None otherwise: the Python code behind it then makes the same checks again and makes the call, or raises what it always raised.  Nothing is kept between calls.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
